@@ -70,14 +70,6 @@ __device__ inline void load_node(const double* nd, int j, St<N, D>& s)
     s.rc2 = nodev<NS, FS>(nd, j, F::RC2);
 }
 
-// left- and right-biased WENO-IS of one characteristic field given on the
-// six stencil nodes; the right-biased value mirrors the stencil (App. C)
-template <typename R>
-__device__ inline void weno_pair(const R* v, double eps, R& l, R& r)
-{
-    weno_is_pair<R>(v, eps, l, r);
-}
-
 // the pair of interpolated values at i+1/2 from v[0..5] = nodes i-2..i+3:
 // App. C weights (WT = 0), or the learned weights (WT = 1) with App. C as the
 // fallback where a learned weight is not finite.  WT = 1 must be reached by
@@ -86,7 +78,7 @@ template <typename R, int WT>
 __device__ inline void interp_pair(const R* v, double eps, const MlpPacked* mlp, R& l, R& r)
 {
     if constexpr (WT == 0) {
-        weno_pair<R>(v, eps, l, r);
+        weno_is_pair(v, eps, l, r);
     } else {
         const R ul[5] = {v[0], v[1], v[2], v[3], v[4]};
         const R ur[5] = {v[5], v[4], v[3], v[2], v[1]};
@@ -95,8 +87,8 @@ __device__ inline void interp_pair(const R* v, double eps, const MlpPacked* mlp,
         mlp_inputs<R>(ur, xr);
         mlp_logits(mlp, xl, zl);
         mlp_logits(mlp, xr, zr);
-        l = mlp_omega(zl, xl, wl) ? mlp_value<R>(ul, wl) : weno_is<R>(v[0], v[1], v[2], v[3], v[4], eps);
-        r = mlp_omega(zr, xr, wr) ? mlp_value<R>(ur, wr) : weno_is<R>(v[5], v[4], v[3], v[2], v[1], eps);
+        l = mlp_omega(zl, xl, wl) ? mlp_value<R>(ul, wl) : weno_is(v[0], v[1], v[2], v[3], v[4], eps);
+        r = mlp_omega(zr, xr, wr) ? mlp_value<R>(ur, wr) : weno_is(v[5], v[4], v[3], v[2], v[1], eps);
     }
 }
 
