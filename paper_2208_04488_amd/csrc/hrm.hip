@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <new>
@@ -210,7 +211,9 @@ __global__ void __launch_bounds__(BS* BA, (sweep_waves<D, DIR, R, WT>())) k_swee
     double G[M], Gp[NA];
     if (live) {
         unsigned lc = 0;
-        face_flux<N, D, DIR, NS, FS, R, WT, true, SLIM>(lds + base(ta, ts), A.e, A.P, A.slot[1 + DIR], G, Gp, lc);
+        const KArg ka = kernel_args();
+        face_flux<N, D, DIR, NS, FS, R, WT, true, SLIM>(
+            lds + base(ta, ts), ka + offsetof(SweepArgs, e), ka + offsetof(SweepArgs, P), A.slot[1 + DIR], G, Gp, lc);
         // face c0+ts is counted once: the last face of a tile is the first
         // face of the next tile unless it is the boundary face nsw
         const int f = c0 + ts;

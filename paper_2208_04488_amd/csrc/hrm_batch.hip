@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <new>
@@ -122,7 +123,6 @@ __global__ void __launch_bounds__(BS, 3) k_batch(const BatchArgs A)
                 const double cb = stage == 0 ? 1.0 : (stage == 1 ? 1.0 / 4.0 : 2.0 / 3.0);
                 for (int c0 = 0; c0 < n; c0 += BS - 1) {
                     const EosDev& e = A.e;
-                    const ParDev& P = A.P;
                     // stage the tile c0-3 .. c0+BS+1 with its primitives
                     // (at raised priority, as in k_sweep)
                     __builtin_amdgcn_s_setprio(3);
@@ -150,7 +150,9 @@ __global__ void __launch_bounds__(BS, 3) k_batch(const BatchArgs A)
                     const bool live = c0 + (ts & ~63) <= n;
                     if (live) {
                         unsigned lc = 0;  // packed counts of this face (cnt_one)
-                        face_flux<N, D, 0, 1, FS, R, 0, false>(lds + ts, e, P, lam, G, Gp, lc);
+                        const KArg ka = kernel_args();
+                        face_flux<N, D, 0, 1, FS, R, 0, false>(lds + ts, ka + offsetof(BatchArgs, e),
+                                                               ka + offsetof(BatchArgs, P), lam, G, Gp, lc);
                         const int f = c0 + ts;  // counted once, as in k_sweep
                         if (f <= n && (ts < BS - 1 || f == n))
 #pragma unroll

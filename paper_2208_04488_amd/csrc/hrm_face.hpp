@@ -104,13 +104,14 @@ __device__ inline R sensor_ratio_t(R v0, R v1, R v2, R v3, R v4)
 }
 
 // Output: G = G^{**,-}_{i+1/2} (M slots) and Gp = alpha slots of G^{**,+}.
+// ke and kp: the species table and the parameters in the kernel arguments.
 // R is the face arithmetic type; node data, the flux limiter and the outputs
 // are double.  LOW = false leaves out the first-order and direct-HRM branches
 // (selected by flags) for callers that never take them.  Always inlined:
 // a call would spill the whole face state around it.
 template <int N, int D, int DIR, int NS, int FS, typename R, int WT = 0, bool LOW = true, bool SLIM = false>
-__device__ __forceinline__ void face_flux(const double* nd, const EosDev& e, const ParDev& P, double lam, double* G, double* Gp,
-                          unsigned& cnt)
+__device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, double lam, double* G, double* Gp,
+                                          unsigned& cnt)
 {
     static_assert(2 * N <= 15, "per-face counts are packed 4 bits per counter");
     using F = NodeFields<N, D, SLIM>;
@@ -150,11 +151,12 @@ __device__ __forceinline__ void face_flux(const double* nd, const EosDev& e, con
             Glo[IA + k] = Glo[IA + k] - ss * Lr.al[k];
         }
     };
-    if (LOW && (P.flags & F_FIRST_ORDER)) {
+    const int flags = kload<ParDev>(kp).flags;
+    if (LOW && (flags & F_FIRST_ORDER)) {
         St<N, D> L, Rn;
         node_pair(L, Rn);
-        if (P.flags & F_FOUR_EQ) {
-            hllc4<N, D, DIR>(e, L, Rn, G);
+        if (flags & F_FOUR_EQ) {
+            hllc4<N, D, DIR>(kload<EosDev>(ke), L, Rn, G);
 #pragma unroll
             for (int k = 0; k < N - 1; ++k) Gp[k] = 0.0;
             return;
@@ -182,7 +184,8 @@ __device__ __forceinline__ void face_flux(const double* nd, const EosDev& e, con
     else
         irc = (R)1 / (rb * cb);
     const R irc2 = irc * irc * rb;
-    const double eps = P.eps_weno;
+    const ParDev Pw = kload<ParDev>(kp);
+    const double eps = Pw.eps_weno;
     // The characteristic fields are interpolated one at a time and each is
     // taken back to its primitive slot (V = R U) at once, so that only the
     // two acoustic fields stay live across the others.
@@ -191,10 +194,10 @@ __device__ __forceinline__ void face_flux(const double* nd, const EosDev& e, con
     R v[6], aL0, aR0, aLM, aRM;
 #pragma unroll
     for (int j = 0; j < 6; ++j) v[j] = dv(j, F::U + DIR) - dv(j, F::P) * irc;
-    interp_pair<R, WT>(v, eps, P.mlp, aL0, aR0);
+    interp_pair<R, WT>(v, eps, Pw.mlp, aL0, aR0);
 #pragma unroll
     for (int j = 0; j < 6; ++j) v[j] = dv(j, F::U + DIR) + dv(j, F::P) * irc;
-    interp_pair<R, WT>(v, eps, P.mlp, aLM, aRM);
+    interp_pair<R, WT>(v, eps, Pw.mlp, aLM, aRM);
     const R dUL = aLM - aL0, dUR = aRM - aR0;
     VL.u[DIR] = back(F::U + DIR, (R)0.5 * (aL0 + aLM));
     VR.u[DIR] = back(F::U + DIR, (R)0.5 * (aR0 + aRM));
@@ -206,7 +209,7 @@ __device__ __forceinline__ void face_flux(const double* nd, const EosDev& e, con
 #pragma unroll
         for (int j = 0; j < 6; ++j) v[j] = dv(j, k) - s * dv(j, F::P);
         R l, r;
-        interp_pair<R, WT>(v, eps, P.mlp, l, r);
+        interp_pair<R, WT>(v, eps, Pw.mlp, l, r);
         VL.ar[k] = back(k, l + arb[k] * h2c * dUL);
         VR.ar[k] = back(k, r + arb[k] * h2c * dUR);
     }
@@ -216,7 +219,7 @@ __device__ __forceinline__ void face_flux(const double* nd, const EosDev& e, con
 #pragma unroll
         for (int j = 0; j < 6; ++j) v[j] = dv(j, F::U + d);
         R l, r;
-        interp_pair<R, WT>(v, eps, P.mlp, l, r);
+        interp_pair<R, WT>(v, eps, Pw.mlp, l, r);
         VL.u[d] = back(F::U + d, l);
         VR.u[d] = back(F::U + d, r);
     }
@@ -225,18 +228,19 @@ __device__ __forceinline__ void face_flux(const double* nd, const EosDev& e, con
 #pragma unroll
         for (int j = 0; j < 6; ++j) v[j] = dv(j, IA + k);
         R l, r;
-        interp_pair<R, WT>(v, eps, P.mlp, l, r);
+        interp_pair<R, WT>(v, eps, Pw.mlp, l, r);
         VL.al[k] = back_d(IA + k, l);
         VR.al[k] = back_d(IA + k, r);
     }
 
     // Sec. 4.3.2 interpolation limiter: left against node i, right against node i+1
-    if (!(P.flags & F_NO_LIMITERS)) {
+    if (!(flags & F_NO_LIMITERS)) {
         St<N, D> L, Rn;
         node_pair(L, Rn);
-        interp_limit<N, D, R>(e, P, VL, convert<N, D, R>(L), cnt);  // also completes the state
-        interp_limit<N, D, R>(e, P, VR, convert<N, D, R>(Rn), cnt);
+        interp_limit<N, D, R>(ke, kp, VL, convert<N, D, R>(L), cnt);  // also completes the state
+        interp_limit<N, D, R>(ke, kp, VR, convert<N, D, R>(Rn), cnt);
     } else {
+        const EosDev e = kload<EosDev>(ke);
         complete_from_prim<N, D, R>(e, VL);
         complete_from_prim<N, D, R>(e, VR);
     }
@@ -248,8 +252,9 @@ __device__ __forceinline__ void face_flux(const double* nd, const EosDev& e, con
     // shock sensor (Sec. 4.3.1) on mixture density and pressure, in double in
     // both variants: C_s = 1e12 turns float rounding of p at a contact into
     // a visible blending weight
+    const ParDev P = kload<ParDev>(kp);
     R sig = 0;
-    if (!(P.flags & F_NO_BLEND)) {
+    if (!(flags & F_NO_BLEND)) {
         double r[6], pr[6];
 #pragma unroll
         for (int j = 0; j < 6; ++j) {
@@ -326,7 +331,7 @@ __device__ __forceinline__ void face_flux(const double* nd, const EosDev& e, con
         Gho_p[k] = Gho[IA + k] - uh * nodev<NS, FS>(nd, 3, IA + k);
         Gho[IA + k] = Gho[IA + k] - uh * nodev<NS, FS>(nd, 2, IA + k);
     }
-    if (P.flags & F_NO_LIMITERS) {
+    if (flags & F_NO_LIMITERS) {
 #pragma unroll
         for (int c = 0; c < M; ++c) G[c] = Gho[c];
 #pragma unroll
@@ -338,7 +343,7 @@ __device__ __forceinline__ void face_flux(const double* nd, const EosDev& e, con
     // interfaces and shocks); the first-order pair is formed only otherwise
     St<N, D> L, Rn;
     node_pair(L, Rn);
-    if (flux_limit_clean<N, D, DIR>(e, P, L, Rn, lam, Gho, Gho_p)) {
+    if (flux_limit_clean<N, D, DIR>(ke, kp, L, Rn, lam, Gho, Gho_p)) {
 #pragma unroll
         for (int c = 0; c < M; ++c) G[c] = Gho[c];
 #pragma unroll
@@ -354,7 +359,7 @@ __device__ __forceinline__ void face_flux(const double* nd, const EosDev& e, con
     if constexpr (sizeof(R) == sizeof(double)) node_pair(Lf, Rf);
     double Glo[M], Glo_p[NA];
     first_order(Lf, Rf, Glo, Glo_p);
-    flux_limit<N, D, DIR>(e, P, Lf, Rf, lam, Gho, Gho_p, Glo, Glo_p, G, Gp, cnt);
+    flux_limit<N, D, DIR>(ke, kp, Lf, Rf, lam, Gho, Gho_p, Glo, Glo_p, G, Gp, cnt);
 }
 
 }  // namespace hrm
