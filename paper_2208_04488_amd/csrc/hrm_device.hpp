@@ -135,6 +135,33 @@ __device__ inline double rcp_newton(double x)
     return fma(fma(-x, r, 1.0), r, r);
 }
 
+// a/b and sqrt(x) to the bit of the IEEE operations where operands and results
+// are normal numbers (and 0 numerators): the reciprocal (root) is refined by
+// one step, to about 1e-15, and the exact remainder of the quotient (root) it
+// gives corrects the result to 1e-30 before the last rounding.  6 and 8
+// instructions instead of the 11 and 18 of the IEEE sequences, whose operand
+// scaling for subnormal and huge numbers no state needs.  A zero, infinite or
+// NaN divisor and a zero, infinite or negative radicand give NaN or infinity.
+__device__ inline double div_rn(double a, double b)
+{
+    const double r0 = __builtin_amdgcn_rcp(b);
+    const double r = fma(fma(-b, r0, 1.0), r0, r0);
+    const double q = a * r;
+    return fma(fma(-b, q, a), r, q);
+}
+__device__ inline double sqrt_rn(double x)
+{
+    const double r = __builtin_amdgcn_rsq(x);
+    double g = x * r, h = 0.5 * r;
+    const double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    return fma(fma(-g, g, x), h, g);
+}
+// float keeps the IEEE operations
+__device__ inline float div_rn(float a, float b) { return a / b; }
+__device__ inline float sqrt_rn(float x) { return sqrt(x); }
+
 // conservative W[M] -> full state (hot-path step a1)
 template <int N, int D>
 __device__ inline void state_from_W(const EosDev& e, const double* W, St<N, D>& s)
@@ -170,7 +197,8 @@ __device__ inline void state_from_W(const EosDev& e, const double* W, St<N, D>& 
     s.p = (re - Pi) * iG;
     s.rc2 = s.p + (s.p + Pi) * iG;
     s.rho = rho;
-    s.c = sqrt(s.rc2 * irho);
+    const double c2 = s.rc2 * irho;
+    s.c = c2 == 0.0 ? 0.0 : sqrt_rn(c2);
 }
 
 // primitive slots (ar, u, p, al[0..N-2]) already set -> the rest of the state
@@ -198,8 +226,8 @@ __device__ inline void complete_from_prim(const EosDev& e, St<N, D, R>& s)
     }
     s.rho = rho;
     s.E = Gam * s.p + Pi + (R)0.5 * rho * u2 + rq;
-    s.rc2 = s.p + (s.p + Pi) / Gam;
-    s.c = sqrt(s.rc2 / rho);
+    s.rc2 = s.p + div_rn(s.p + Pi, Gam);
+    s.c = sqrt_rn(div_rn(s.rc2, rho));
 }
 
 // rho(e - qbar) of a conservative vector
@@ -364,13 +392,13 @@ __device__ inline R hllc(const St<N, D, R>& L, const St<N, D, R>& Rs, double* G)
     const R sL = fmin(ub - cb, uL - L.c);
     const R sR = fmax(ub + cb, uR + Rs.c);
     const R dL = sL - uL, dR = sR - uR;
-    const R ss = (Rs.p - L.p + L.rho * uL * dL - Rs.rho * uR * dR) / (L.rho * dL - Rs.rho * dR);
+    const R ss = div_rn(Rs.p - L.p + L.rho * uL * dL - Rs.rho * uR * dR, L.rho * dL - Rs.rho * dR);
     const R sg = ss > (R)0 ? (R)1 : (ss < (R)0 ? (R)-1 : (R)0);
     const R wl = (R)0.5 * ((R)1 + sg), wr = (R)0.5 * ((R)1 - sg);
     const R sm = fmin((R)0, sL), sp = fmax((R)0, sR);
     if constexpr (sizeof(R) == sizeof(double)) {
         // star states U*_K = chi_K (...) with chi_K = (s_K - u_K) / (s_K - s*)
-        const R chiL = dL / (sL - ss), chiR = dR / (sR - ss);
+        const R chiL = div_rn(dL, sL - ss), chiR = div_rn(dR, sR - ss);
 #pragma unroll
         for (int k = 0; k < N; ++k)
             G[k] = wl * (L.ar[k] * uL + sm * (chiL * L.ar[k] - L.ar[k])) +
@@ -383,8 +411,8 @@ __device__ inline R hllc(const St<N, D, R>& L, const St<N, D, R>& Rs, double* G)
             const R WsR = d == DIR ? chiR * Rs.rho * ss : chiR * Rs.rho * Rs.u[d];
             G[N + d] = wl * (FLd + sm * (WsL - L.mom[d])) + wr * (FRd + sp * (WsR - Rs.mom[d]));
         }
-        const R EsL = chiL * (L.E + (ss - uL) * (L.rho * ss + L.p / dL));
-        const R EsR = chiR * (Rs.E + (ss - uR) * (Rs.rho * ss + Rs.p / dR));
+        const R EsL = chiL * (L.E + (ss - uL) * (L.rho * ss + div_rn(L.p, dL)));
+        const R EsR = chiR * (Rs.E + (ss - uR) * (Rs.rho * ss + div_rn(Rs.p, dR)));
         G[IE] = wl * ((L.E + L.p) * uL + sm * (EsL - L.E)) + wr * ((Rs.E + Rs.p) * uR + sp * (EsR - Rs.E));
     } else {
         // float: the jumps U*_K - U_K in closed form.  chi_K - 1 =
@@ -554,7 +582,7 @@ __device__ inline bool flux_limit_clean(KArg ke, KArg kp, const St<N, D>& L, con
     }
     ok = ok && 1.0 - sp >= P.eps_f_a && 1.0 - sm >= P.eps_f_a;
     // rho (e - qbar) of each half-cell state, as rhoe_tilde forms it
-    const double rep = Ep - 0.5 * m2p / rp - qp, rem = Em - 0.5 * m2m / rm - qm;
+    const double rep = Ep - div_rn(0.5 * m2p, rp) - qp, rem = Em - div_rn(0.5 * m2m, rm) - qm;
     return ok && rep >= P.eps_f_re && rem >= P.eps_f_re && isfinite(rep) && isfinite(rem);
 }
 
@@ -779,9 +807,9 @@ __device__ inline void block_max(double* m, double* sh)
 // rho_k(p, T) for k < N-1, and leaves W unchanged where relaxed_pT fails.
 // The root is ill-conditioned in a liquid at low pressure (its condition number
 // grows like gamma_1 pinf_1 / p), so this function evaluates each formula in
-// the order written, with IEEE division and no FMA contraction: its rounding
-// is then reproducible by any plain double-precision evaluation of the same
-// formulas.
+// the order written, with divisions and roots that round as the IEEE ones
+// do (div_rn, sqrt_rn) and no FMA contraction: its rounding is then
+// reproducible by any plain double-precision evaluation of the same formulas.
 template <int N, int D>
 __device__ inline bool relaxed_pT(const EosDev& e, const double* W, double& p_out, double& T_out)
 {
@@ -793,7 +821,7 @@ __device__ inline bool relaxed_pT(const EosDev& e, const double* W, double& p_ou
     double cvb = 0.0, cpb = 0.0, qb = 0.0, Y0 = 0.0;
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-        const double Y = W[k] / rho;  // mass fraction
+        const double Y = div_rn(W[k], rho);  // mass fraction
         cvb += Y * e.cv[k];
         cpb += Y * e.g[k] * e.cv[k];
         qb += Y * e.q[k];
@@ -802,7 +830,7 @@ __device__ inline bool relaxed_pT(const EosDev& e, const double* W, double& p_ou
     double m2 = 0.0;
 #pragma unroll
     for (int d = 0; d < D; ++d) m2 += W[N + d] * W[N + d];
-    const double re = W[IE] - 0.5 * m2 / rho - rho * qb;  // rho (e - qbar)
+    const double re = W[IE] - div_rn(0.5 * m2, rho) - rho * qb;  // rho (e - qbar)
     if (!(re > 0.0) || !(rho > 0.0)) return false;
     const double p1 = e.pinf[0];
     const double R1 = e.g[0] * e.cv[0] - e.cv[0];  // c_p1 - c_v1
@@ -812,12 +840,12 @@ __device__ inline bool relaxed_pT(const EosDev& e, const double* W, double& p_ou
     const double disc = B * B - 4.0 * A * C;
     double p;
     if (B <= 0.0)
-        p = (-B + sqrt(disc)) / (2.0 * A);
+        p = div_rn(-B + sqrt_rn(disc), 2.0 * A);
     else
-        p = 2.0 * C / (-B - sqrt(disc));
+        p = div_rn(2.0 * C, -B - sqrt_rn(disc));
     if (!(p > 0.0) || !isfinite(p)) return false;
-    const double e_t = re / rho;
-    const double T = e_t / (Y0 * (p + e.g[0] * p1) * e.cv[0] / (p + p1) + cvb - Y0 * e.cv[0]);
+    const double e_t = div_rn(re, rho);
+    const double T = div_rn(e_t, div_rn(Y0 * (p + e.g[0] * p1) * e.cv[0], p + p1) + cvb - Y0 * e.cv[0]);
     if (!(T > 0.0) || !isfinite(T)) return false;
     p_out = p;
     T_out = T;
@@ -833,8 +861,8 @@ __device__ inline bool relax_cell(const EosDev& e, double* W)
     if (!relaxed_pT<N, D>(e, W, p, T)) return false;
 #pragma unroll
     for (int k = 0; k < N - 1; ++k) {
-        const double rk = (p + e.pinf[k]) / ((e.g[k] - 1.0) * e.cv[k] * T);  // rho_k(p, T)
-        W[IA + k] = W[k] / rk;
+        const double rk = div_rn(p + e.pinf[k], (e.g[k] - 1.0) * e.cv[k] * T);  // rho_k(p, T)
+        W[IA + k] = div_rn(W[k], rk);
     }
     return true;
 }
@@ -876,10 +904,10 @@ __device__ inline void hrm4_pc(const EosDev& e, const St<N, D>& s, double& p, do
     }
 #pragma unroll
     for (int d = 0; d < D; ++d) m2 += s.mom[d] * s.mom[d];
-    const double re = s.E - 0.5 * m2 / rho - rq;
+    const double re = s.E - div_rn(0.5 * m2, rho) - rq;
     const double S2 = SR - s.ar[0] * (e.cp[0] - e.cv[0]);
     const double p1 = e.pinf[0];
-    c = sqrt(p * (re + p) * (SR * p + p1 * S2) / (rho * (Sv * p * p + re * p1 * S2)));
+    c = sqrt_rn(div_rn(p * (re + p) * (SR * p + p1 * S2), rho * (Sv * p * p + re * p1 * S2)));
 }
 
 // First-order HLLC for the four-equation HRM solved directly, in direction
@@ -898,11 +926,11 @@ __device__ inline void hllc4(const EosDev& e, const St<N, D>& L, const St<N, D>&
     const double sL = fmin(ub - cb, uL - cL);
     const double sR = fmax(ub + cb, uR + cR);
     const double dL = sL - uL, dR = sR - uR;
-    const double ss = (pR - pL + L.rho * uL * dL - Rs.rho * uR * dR) / (L.rho * dL - Rs.rho * dR);
+    const double ss = div_rn(pR - pL + L.rho * uL * dL - Rs.rho * uR * dR, L.rho * dL - Rs.rho * dR);
     const double sg = ss > 0.0 ? 1.0 : (ss < 0.0 ? -1.0 : 0.0);
     const double wl = 0.5 * (1.0 + sg), wr = 0.5 * (1.0 - sg);
     const double sm = fmin(0.0, sL), sp = fmax(0.0, sR);
-    const double chiL = dL / (sL - ss), chiR = dR / (sR - ss);
+    const double chiL = div_rn(dL, sL - ss), chiR = div_rn(dR, sR - ss);
 #pragma unroll
     for (int k = 0; k < N; ++k)
         G[k] = wl * (L.ar[k] * uL + sm * (chiL * L.ar[k] - L.ar[k])) +
@@ -915,8 +943,8 @@ __device__ inline void hllc4(const EosDev& e, const St<N, D>& L, const St<N, D>&
         const double WsR = d == DIR ? chiR * Rs.rho * ss : chiR * Rs.rho * Rs.u[d];
         G[N + d] = wl * (FLd + sm * (WsL - L.mom[d])) + wr * (FRd + sp * (WsR - Rs.mom[d]));
     }
-    const double EsL = chiL * (L.E + (ss - uL) * (L.rho * ss + pL / dL));
-    const double EsR = chiR * (Rs.E + (ss - uR) * (Rs.rho * ss + pR / dR));
+    const double EsL = chiL * (L.E + (ss - uL) * (L.rho * ss + div_rn(pL, dL)));
+    const double EsR = chiR * (Rs.E + (ss - uR) * (Rs.rho * ss + div_rn(pR, dR)));
     G[IE] = wl * ((L.E + pL) * uL + sm * (EsL - L.E)) + wr * ((Rs.E + pR) * uR + sp * (EsR - Rs.E));
 #pragma unroll
     for (int k = 0; k < N - 1; ++k) G[IA + k] = 0.0;
