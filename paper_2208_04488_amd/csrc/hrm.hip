@@ -1002,6 +1002,7 @@ int hrm_create(const hrm_grid* g, const hrm_eos* e, const hrm_params* prm, hrm_c
     P.flags = g->flags;
     if (g->flags & HRM_FOUR_EQ) P.flags |= HRM_FIRST_ORDER;  // the direct HRM solver is first order
     P.fast_flux_limiter = p.eps_f_ar >= p.hs_f_ar && p.eps_f_a >= p.hs_f_a && p.eps_f_re >= p.hs_f_re;
+    P.fast_interp_limiter = p.eps_i_ar >= p.hs_i_ar && p.eps_i_a >= p.hs_i_a;
 
     const size_t bytes = sizeof(double) * (size_t)c->M * (size_t)c->ncell;
     c->npart = (int)std::min<long long>((c->ncell + 255) / 256, 2048);

@@ -348,6 +348,7 @@ int hrm_batch_create(const hrm_eos* e, const hrm_params* prm, int nprob, const l
     P.hcs_c = 3.0 * p.psi / 256.0 - 1.0 / 60.0;
     P.flags = 0;
     P.fast_flux_limiter = p.eps_f_ar >= p.hs_f_ar && p.eps_f_a >= p.hs_f_a && p.eps_f_re >= p.hs_f_re;
+    P.fast_interp_limiter = p.eps_i_ar >= p.hs_i_ar && p.eps_i_a >= p.hs_i_a;
     // default launch: 256 threads, three workgroups per CU (the kernel's
     // register budget admits three waves per SIMD), 10 steps per launch
     int dev = 0, cus = 256;

@@ -41,7 +41,8 @@ struct ParDev {
     double Cs, qexp, psi;
     double hcs_a, hcs_b, hcs_c;  // eq:reconstructed_G coefficients from psi
     int flags;
-    int fast_flux_limiter;  // eps_f >= eps_f^HS for all three quantities
+    int fast_flux_limiter;    // eps_f >= eps_f^HS for all three quantities
+    int fast_interp_limiter;  // eps_i >= eps_i^HS for both quantities
     const MlpPacked* mlp;   // packed network of the learned weights (device), or null
 };
 
@@ -450,6 +451,25 @@ __device__ inline double lim_theta(double a, double b, double eps)
     return b < m ? (a - m) / (a - b) : 1.0;
 }
 
+// Completes an interpolated primitive state V and tells whether the limiter
+// below would leave it as it is, without looking at the node: every partial
+// density and volume fraction at or above eps (then b >= eps >= min(eps, a):
+// no blending, and with eps >= eps^HS no hard switch), rho c^2 at or above
+// eps^HS, and everything finite (an infinite or NaN slot leaves a bound unmet
+// or makes E or rho c^2 infinite or NaN).  Most faces pass; the nodes are
+// read from LDS and the limiter runs only where one does not.
+template <int N, int D, typename R>
+__device__ inline bool interp_clean(KArg ke, KArg kp, St<N, D, R>& V)
+{
+    const EosDev e = kload<EosDev>(ke);
+    const ParDev P = kload<ParDev>(kp);
+    complete_from_prim<N, D, R>(e, V);
+    bool ok = P.fast_interp_limiter != 0;
+#pragma unroll
+    for (int k = 0; k < N; ++k) ok = ok & ((double)V.ar[k] >= P.eps_i_ar) & (V.al[k] >= P.eps_i_a);
+    return ok & ((double)V.rc2 >= P.hs_i_rc2) & isfinite(V.rc2) & isfinite(V.E);
+}
+
 // Sec. 4.3.2 interpolation limiter on an interpolated primitive state V
 // (partial densities and volume fractions are blended toward the node state;
 // velocity and pressure are kept), then the hard switch to the node state.
@@ -552,7 +572,7 @@ __device__ inline bool flux_limit_clean(KArg ke, KArg kp, const St<N, D>& L, con
     for (int k = 0; k < N; ++k) {
         const double wp = L.ar[k] - l2 * (Gho[k] - L.ar[k] * uL);
         const double wm = R.ar[k] + l2 * (Gho[k] - R.ar[k] * uR);
-        ok = ok && wp >= P.eps_f_ar && wm >= P.eps_f_ar && isfinite(Gho[k]) && isfinite(wp) && isfinite(wm);
+        ok = ok & (wp >= P.eps_f_ar) & (wm >= P.eps_f_ar);
         rp += wp;
         rm += wm;
         qp += wp * e.q[k];
@@ -563,27 +583,26 @@ __device__ inline bool flux_limit_clean(KArg ke, KArg kp, const St<N, D>& L, con
     for (int d = 0; d < D; ++d) {
         const double wp = L.mom[d] - l2 * (Gho[N + d] - (L.mom[d] * uL + (d == DIR ? L.p : 0.0)));
         const double wm = R.mom[d] + l2 * (Gho[N + d] - (R.mom[d] * uR + (d == DIR ? R.p : 0.0)));
-        ok = ok && isfinite(Gho[N + d]) && isfinite(wp) && isfinite(wm);
         m2p += wp * wp;
         m2m += wm * wm;
     }
     const double Ep = L.E - l2 * (Gho[IE] - (L.E + L.p) * uL);
     const double Em = R.E + l2 * (Gho[IE] - (R.E + R.p) * uR);
-    ok = ok && isfinite(Gho[IE]) && isfinite(Ep) && isfinite(Em);
     double sp = 0.0, sm = 0.0;
 #pragma unroll
     for (int k = 0; k < N - 1; ++k) {
-        const double ap = L.al[k] - l2 * (Gho[IA + k] - 0.0);
-        const double am = R.al[k] + l2 * (Gho_p[k] - 0.0);
-        ok = ok && ap >= P.eps_f_a && am >= P.eps_f_a && isfinite(Gho[IA + k]) && isfinite(Gho_p[k]) &&
-             isfinite(ap) && isfinite(am);
+        const double ap = L.al[k] - l2 * Gho[IA + k];
+        const double am = R.al[k] + l2 * Gho_p[k];
+        ok = ok & (ap >= P.eps_f_a) & (am >= P.eps_f_a);
         sp += ap;
         sm += am;
     }
-    ok = ok && 1.0 - sp >= P.eps_f_a && 1.0 - sm >= P.eps_f_a;
-    // rho (e - qbar) of each half-cell state, as rhoe_tilde forms it
-    const double rep = Ep - div_rn(0.5 * m2p, rp) - qp, rem = Em - div_rn(0.5 * m2m, rm) - qm;
-    return ok && rep >= P.eps_f_re && rem >= P.eps_f_re && isfinite(rep) && isfinite(rem);
+    ok = ok & (1.0 - sp >= P.eps_f_a) & (1.0 - sm >= P.eps_f_a);
+    // rho (e - qbar) >= eps of each half-cell state, times rho (positive by the
+    // bounds above).  An infinite or NaN slot fails its bound or leaves these
+    // two products infinite or NaN.
+    const double tp = (Ep - qp - P.eps_f_re) * rp - 0.5 * m2p, tm = (Em - qm - P.eps_f_re) * rm - 0.5 * m2m;
+    return ok & (tp >= 0.0) & (tm >= 0.0) & isfinite(tp) & isfinite(tm);
 }
 
 template <int N, int D, int DIR>

@@ -235,10 +235,13 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
 
     // Sec. 4.3.2 interpolation limiter: left against node i, right against node i+1
     if (!(flags & F_NO_LIMITERS)) {
-        St<N, D> L, Rn;
-        node_pair(L, Rn);
-        interp_limit<N, D, R>(ke, kp, VL, convert<N, D, R>(L), cnt);  // also completes the state
-        interp_limit<N, D, R>(ke, kp, VR, convert<N, D, R>(Rn), cnt);
+        const bool cl = interp_clean<N, D, R>(ke, kp, VL), cr = interp_clean<N, D, R>(ke, kp, VR);
+        if (__builtin_expect(!(cl & cr), 0)) {
+            St<N, D> L, Rn;
+            node_pair(L, Rn);
+            interp_limit<N, D, R>(ke, kp, VL, convert<N, D, R>(L), cnt);  // also completes the state
+            interp_limit<N, D, R>(ke, kp, VR, convert<N, D, R>(Rn), cnt);
+        }
     } else {
         const EosDev e = kload<EosDev>(ke);
         complete_from_prim<N, D, R>(e, VL);
