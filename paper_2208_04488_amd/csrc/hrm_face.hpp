@@ -92,15 +92,37 @@ __device__ inline void interp_pair(const R* v, double eps, const MlpPacked* mlp,
     }
 }
 
-// normalised fourth-order second derivative of the shock sensor (Sec. 4.3.1)
-template <typename R>
-__device__ inline R sensor_ratio_t(R v0, R v1, R v2, R v3, R v4)
+// numerator and denominator (both >= 0) of the shock sensor's normalised
+// fourth-order second derivative (Sec. 4.3.1)
+__device__ inline void sensor_parts(double v0, double v1, double v2, double v3, double v4, double& num, double& den)
 {
-    const R num = fabs(-v0 + (R)16 * v1 - (R)30 * v2 + (R)16 * v3 - v4);
-    const R den = fabs(v0 + (R)16 * v1 + (R)30 * v2 + (R)16 * v3 + v4);
-    if constexpr (sizeof(R) == sizeof(double))
-        if (den > 1e-290) return num * rcp_newton(den);  // densities and pressures: far from subnormal
-    return den > (R)0 ? num / den : (num > (R)0 ? (R)1 : (R)0);
+    const double a = v1 + v3, y = fma(30.0, v2, v0 + v4);
+    num = fabs(fma(16.0, a, -y));
+    den = fabs(fma(16.0, a, y));
+}
+
+// the ratio itself; a zero denominator (a liquid under tension) gives 1 if
+// the numerator is non-zero, else 0
+__device__ inline double sensor_ratio(double num, double den)
+{
+    return den > 0.0 ? num / den : (num > 0.0 ? 1.0 : 0.0);
+}
+
+// product of the mean ratios of density and pressure over the two nodes of
+// the face: one quotient for the four ratios, unless the product of their
+// denominators leaves the range where it is a normal number
+__device__ inline double sensor_product(const double* r, const double* p)
+{
+    double n[4], d[4];
+    sensor_parts(r[0], r[1], r[2], r[3], r[4], n[0], d[0]);
+    sensor_parts(r[1], r[2], r[3], r[4], r[5], n[1], d[1]);
+    sensor_parts(p[0], p[1], p[2], p[3], p[4], n[2], d[2]);
+    sensor_parts(p[1], p[2], p[3], p[4], p[5], n[3], d[3]);
+    const double dr = d[0] * d[1], dp = d[2] * d[3], dd = dr * dp;
+    if (__builtin_expect(dr > 1e-140 && dp > 1e-140 && dd < 1e290, 1))
+        return 0.25 * quot_newton(fma(n[0], d[1], n[1] * d[0]) * fma(n[2], d[3], n[3] * d[2]), dd);
+    return 0.25 * (sensor_ratio(n[0], d[0]) + sensor_ratio(n[1], d[1])) *
+           (sensor_ratio(n[2], d[2]) + sensor_ratio(n[3], d[3]));
 }
 
 // Output: G = G^{**,-}_{i+1/2} (M slots) and Gp = alpha slots of G^{**,+}.
@@ -264,11 +286,7 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
             r[j] = node_rho<F, N, NS, FS>(nd, j);
             pr[j] = nodev<NS, FS>(nd, j, F::P);
         }
-        const double sr = 0.5 * (sensor_ratio_t<double>(r[1], r[2], r[3], r[4], r[5]) +
-                                 sensor_ratio_t<double>(r[0], r[1], r[2], r[3], r[4]));
-        const double sp = 0.5 * (sensor_ratio_t<double>(pr[1], pr[2], pr[3], pr[4], pr[5]) +
-                                 sensor_ratio_t<double>(pr[0], pr[1], pr[2], pr[3], pr[4]));
-        const double z = sr * sp;
+        const double z = sensor_product(r, pr);
         const double arg = P.Cs * (P.qexp == 2.0 ? z * z : pow(z, P.qexp));
         // tanh is exactly 0 at 0 and rounds to 1 for arguments >= 22; below
         // 0.01 (smooth flow: nearly every face) its odd series to x^7 is
@@ -287,46 +305,75 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
     // Volume-fraction slots and the face velocity u-hat are double in both
     // variants: G^+-_alpha = G_alpha - u-hat alpha_i cancels to (alpha-tilde -
     // alpha_i) u-hat only if both terms see the same velocity at full precision.
-    const R psi = (R)P.psi, ha = (R)P.hcs_a, hb = (R)P.hcs_b, hc = (R)P.hcs_c;
-    const double psid = P.psi, had = P.hcs_a, hbd = P.hcs_b, hcd = P.hcs_c;
-    R un[6], pj[6];
-    double und[6];
+    double Gho[M], Gho_p[NA], uh;
+    if constexpr (!DELTA) {
+        // every slot's flux at node j is its conserved value times u_j (plus
+        // pressure terms), so the node weights of the reconstruction are
+        // multiplied into u_j once and each slot is six multiply-adds
+        const double wt[6] = {-P.hcs_c, P.hcs_b, -P.hcs_a, -P.hcs_a, P.hcs_b, -P.hcs_c};
+        double cu[6], pw = 0.0, epw = 0.0;
+        uh = P.psi * ut;
 #pragma unroll
-    for (int j = 0; j < 6; ++j) {
-        und[j] = nodev<NS, FS>(nd, j, F::U + DIR);
-        un[j] = (R)und[j];
-        pj[j] = nv(j, F::P);
-    }
-    double Gho[M], Gho_p[NA];
-    const double sigd = sig;
-#pragma unroll
-    for (int c = 0; c < M; ++c) {
-        if (c >= IA) {
-            double g[6];
-#pragma unroll
-            for (int j = 0; j < 6; ++j) g[j] = nodev<NS, FS>(nd, j, c) * und[j];
-            const double ghcs = psid * Gt[c] - had * (g[2] + g[3]) + hbd * (g[1] + g[4]) - hcd * (g[0] + g[5]);
-            Gho[c] = sigd * Gt[c] + (1.0 - sigd) * ghcs;
-        } else {
-            R g[6];
-#pragma unroll
-            for (int j = 0; j < 6; ++j) {
-                const R w = nv(j, c);
-                if (c >= N && c < N + D)
-                    g[j] = w * un[j] + (c - N == DIR ? pj[j] : (R)0);
-                else if (c == IE)
-                    g[j] = (w + pj[j]) * un[j];
-                else
-                    g[j] = w * un[j];
-            }
-            const R gt = (R)Gt[c];
-            const R ghcs = psi * gt - ha * (g[2] + g[3]) + hb * (g[1] + g[4]) - hc * (g[0] + g[5]);
-            Gho[c] = (double)(sig * gt + ((R)1 - sig) * ghcs);
+        for (int j = 0; j < 6; ++j) {
+            cu[j] = wt[j] * nodev<NS, FS>(nd, j, F::U + DIR);
+            const double pj = nodev<NS, FS>(nd, j, F::P);
+            uh += cu[j];
+            pw = fma(wt[j], pj, pw);
+            epw = fma(cu[j], pj, epw);
         }
+        const double om = 1.0 - sig;  // 0 where the sensor is 1: nothing of h is left then
+        uh = fma(sig, ut, om * uh);
+#pragma unroll
+        for (int c = 0; c < M; ++c) {
+            double h = P.psi * Gt[c];
+            if (c == N + DIR) h += pw;
+            if (c == IE) h += epw;
+#pragma unroll
+            for (int j = 0; j < 6; ++j) h = fma(cu[j], nodev<NS, FS>(nd, j, c), h);
+            Gho[c] = fma(sig, Gt[c], om * h);
+        }
+    } else {
+        const R psi = (R)P.psi, ha = (R)P.hcs_a, hb = (R)P.hcs_b, hc = (R)P.hcs_c;
+        const double psid = P.psi, had = P.hcs_a, hbd = P.hcs_b, hcd = P.hcs_c;
+        R un[6], pj[6];
+        double und[6];
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+            und[j] = nodev<NS, FS>(nd, j, F::U + DIR);
+            un[j] = (R)und[j];
+            pj[j] = nv(j, F::P);
+        }
+        const double sigd = sig;
+#pragma unroll
+        for (int c = 0; c < M; ++c) {
+            if (c >= IA) {
+                double g[6];
+#pragma unroll
+                for (int j = 0; j < 6; ++j) g[j] = nodev<NS, FS>(nd, j, c) * und[j];
+                const double ghcs = psid * Gt[c] - had * (g[2] + g[3]) + hbd * (g[1] + g[4]) - hcd * (g[0] + g[5]);
+                Gho[c] = sigd * Gt[c] + (1.0 - sigd) * ghcs;
+            } else {
+                R g[6];
+#pragma unroll
+                for (int j = 0; j < 6; ++j) {
+                    const R w = nv(j, c);
+                    if (c >= N && c < N + D)
+                        g[j] = w * un[j] + (c - N == DIR ? pj[j] : (R)0);
+                    else if (c == IE)
+                        g[j] = (w + pj[j]) * un[j];
+                    else
+                        g[j] = w * un[j];
+                }
+                const R gt = (R)Gt[c];
+                const R ghcs = psi * gt - ha * (g[2] + g[3]) + hb * (g[1] + g[4]) - hc * (g[0] + g[5]);
+                Gho[c] = (double)(sig * gt + ((R)1 - sig) * ghcs);
+            }
+        }
+        const double utd = ut;
+        const double uhcs =
+            psid * utd - had * (und[2] + und[3]) + hbd * (und[1] + und[4]) - hcd * (und[0] + und[5]);
+        uh = sigd * utd + (1.0 - sigd) * uhcs;
     }
-    const double utd = ut;
-    const double uhcs = psid * utd - had * (und[2] + und[3]) + hbd * (und[1] + und[4]) - hcd * (und[0] + und[5]);
-    const double uh = sigd * utd + (1.0 - sigd) * uhcs;
 
     // high-order quasi-conservative pair: alpha slots minus u-hat alpha_i / alpha_{i+1}
 #pragma unroll
