@@ -382,62 +382,87 @@ __device__ inline void weno_is_pair(const float* v, double eps, float& l, float&
     }
 }
 
+// wave speed estimates of Sec. 4.1.1 and the contact speed
+template <typename R>
+__device__ inline R hllc_speeds(R uL, R uR, R pL, R pR, R rhoL, R rhoR, R cL, R cR, R& sL, R& sR)
+{
+    const R ub = (R)0.5 * (uL + uR), cb = (R)0.5 * (cL + cR);
+    sL = fmin(ub - cb, uL - cL);
+    sR = fmax(ub + cb, uR + cR);
+    const R dL = sL - uL, dR = sR - uR;
+    return div_rn(pR - pL + rhoL * uL * dL - rhoR * uR * dR, rhoL * dL - rhoR * dR);
+}
+
 // Sec. 4.1.1 HLLC for the five-equation model in direction DIR.  Writes
-// G = F^HLLC + (0, ..., f_alpha) and returns s_*.  sign(0) = 0.
-template <int N, int D, int DIR, typename R>
-__device__ inline R hllc(const St<N, D, R>& L, const St<N, D, R>& Rs, double* G)
+// G = F^HLLC + (0, ..., f_alpha) and returns s_*.
+//
+// The jumps U*_K - U_K are taken in closed form, with q_K = (s* - u_K) /
+// (s_K - s*) = chi_K - 1: q U for the slots that the contact carries, rho s_K
+// q for the normal momentum, q (E + p + rho s* (s_K - u_K)) for the energy.
+// In double only the side that the flux is taken from is evaluated: K = L for
+// s* >= 0, else R (at s* = 0 both sides give the same flux, p* in the normal
+// momentum and 0 elsewhere, so either stands for their average).  That needs
+// two divisions instead of five and half of the flux arithmetic.
+template <int N, int D, int DIR>
+__device__ inline double hllc(const St<N, D>& L, const St<N, D>& Rs, double* G)
 {
     constexpr int IE = N + D, IA = N + D + 1;
+    double sL, sR;
+    const double ss =
+        hllc_speeds<double>(L.u[DIR], Rs.u[DIR], L.p, Rs.p, L.rho, Rs.rho, L.c, Rs.c, sL, sR);
+    const bool left = ss >= 0.0;
+    auto pick = [&](double a, double b) { return left ? a : b; };
+    const double u = pick(L.u[DIR], Rs.u[DIR]), p = pick(L.p, Rs.p), rho = pick(L.rho, Rs.rho);
+    const double E = pick(L.E, Rs.E), sk = pick(sL, sR), cap = pick(fmin(0.0, sL), fmax(0.0, sR));
+    const double cq = cap * div_rn(ss - u, sk - ss);
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const double a = pick(L.ar[k], Rs.ar[k]);
+        G[k] = fma(cq, a, a * u);
+    }
+    const double m = rho * u;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        const double md = d == DIR ? m : rho * pick(L.u[d], Rs.u[d]);
+        G[N + d] = d == DIR ? fma(cq, rho * sk, fma(m, u, p)) : fma(cq, md, md * u);
+    }
+    const double h = E + p;
+    G[IE] = fma(cq, fma(rho * ss, sk - u, h), h * u);
+#pragma unroll
+    for (int k = 0; k < N - 1; ++k) G[IA + k] = pick(L.al[k], Rs.al[k]) * ss;
+    return ss;
+}
+
+// float: both sides, averaged at s* = 0 (sign(0) = 0).  chi_K U_K - U_K would
+// round to 0 and drop the star-state correction of the flux where |s_K| (a
+// liquid's sound speed) dwarfs |s* - u_K|, hence the closed form here too.
+template <int N, int D, int DIR>
+__device__ inline float hllc(const St<N, D, float>& L, const St<N, D, float>& Rs, double* G)
+{
+    using R = float;
+    constexpr int IE = N + D, IA = N + D + 1;
+    R sL, sR;
     const R uL = L.u[DIR], uR = Rs.u[DIR];
-    const R ub = (R)0.5 * (uL + uR), cb = (R)0.5 * (L.c + Rs.c);
-    const R sL = fmin(ub - cb, uL - L.c);
-    const R sR = fmax(ub + cb, uR + Rs.c);
+    const R ss = hllc_speeds<R>(uL, uR, L.p, Rs.p, L.rho, Rs.rho, L.c, Rs.c, sL, sR);
     const R dL = sL - uL, dR = sR - uR;
-    const R ss = div_rn(Rs.p - L.p + L.rho * uL * dL - Rs.rho * uR * dR, L.rho * dL - Rs.rho * dR);
     const R sg = ss > (R)0 ? (R)1 : (ss < (R)0 ? (R)-1 : (R)0);
     const R wl = (R)0.5 * ((R)1 + sg), wr = (R)0.5 * ((R)1 - sg);
     const R sm = fmin((R)0, sL), sp = fmax((R)0, sR);
-    if constexpr (sizeof(R) == sizeof(double)) {
-        // star states U*_K = chi_K (...) with chi_K = (s_K - u_K) / (s_K - s*)
-        const R chiL = div_rn(dL, sL - ss), chiR = div_rn(dR, sR - ss);
+    const R qL = (ss - uL) / (sL - ss), qR = (ss - uR) / (sR - ss);
 #pragma unroll
-        for (int k = 0; k < N; ++k)
-            G[k] = wl * (L.ar[k] * uL + sm * (chiL * L.ar[k] - L.ar[k])) +
-                   wr * (Rs.ar[k] * uR + sp * (chiR * Rs.ar[k] - Rs.ar[k]));
+    for (int k = 0; k < N; ++k)
+        G[k] = wl * (L.ar[k] * uL + sm * (qL * L.ar[k])) + wr * (Rs.ar[k] * uR + sp * (qR * Rs.ar[k]));
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            const R FLd = L.mom[d] * uL + (d == DIR ? L.p : (R)0);
-            const R FRd = Rs.mom[d] * uR + (d == DIR ? Rs.p : (R)0);
-            const R WsL = d == DIR ? chiL * L.rho * ss : chiL * L.rho * L.u[d];
-            const R WsR = d == DIR ? chiR * Rs.rho * ss : chiR * Rs.rho * Rs.u[d];
-            G[N + d] = wl * (FLd + sm * (WsL - L.mom[d])) + wr * (FRd + sp * (WsR - Rs.mom[d]));
-        }
-        const R EsL = chiL * (L.E + (ss - uL) * (L.rho * ss + div_rn(L.p, dL)));
-        const R EsR = chiR * (Rs.E + (ss - uR) * (Rs.rho * ss + div_rn(Rs.p, dR)));
-        G[IE] = wl * ((L.E + L.p) * uL + sm * (EsL - L.E)) + wr * ((Rs.E + Rs.p) * uR + sp * (EsR - Rs.E));
-    } else {
-        // float: the jumps U*_K - U_K in closed form.  chi_K - 1 =
-        // (s* - u_K) / (s_K - s*) is far below float resolution when |s_K|
-        // (a liquid's sound speed) dwarfs |s* - u_K|; chi_K U_K - U_K would
-        // then round to 0 and drop the star-state correction of the flux.
-        const R qL = (ss - uL) / (sL - ss), qR = (ss - uR) / (sR - ss);
-#pragma unroll
-        for (int k = 0; k < N; ++k)
-            G[k] = wl * (L.ar[k] * uL + sm * (qL * L.ar[k])) + wr * (Rs.ar[k] * uR + sp * (qR * Rs.ar[k]));
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            const R FLd = L.mom[d] * uL + (d == DIR ? L.p : (R)0);
-            const R FRd = Rs.mom[d] * uR + (d == DIR ? Rs.p : (R)0);
-            // chi (rho s*) - rho u = rho s_K q_K along DIR; chi m_d - m_d = q_K m_d across
-            const R JL = d == DIR ? L.rho * sL * qL : qL * L.mom[d];
-            const R JR = d == DIR ? Rs.rho * sR * qR : qR * Rs.mom[d];
-            G[N + d] = wl * (FLd + sm * JL) + wr * (FRd + sp * JR);
-        }
-        // E*_K - E_K = q_K (E_K + p_K + rho_K s* (s_K - u_K))
-        const R JL = qL * (L.E + L.p + L.rho * ss * dL);
-        const R JR = qR * (Rs.E + Rs.p + Rs.rho * ss * dR);
-        G[IE] = wl * ((L.E + L.p) * uL + sm * JL) + wr * ((Rs.E + Rs.p) * uR + sp * JR);
+    for (int d = 0; d < D; ++d) {
+        const R FLd = L.mom[d] * uL + (d == DIR ? L.p : (R)0);
+        const R FRd = Rs.mom[d] * uR + (d == DIR ? Rs.p : (R)0);
+        const R JL = d == DIR ? L.rho * sL * qL : qL * L.mom[d];
+        const R JR = d == DIR ? Rs.rho * sR * qR : qR * Rs.mom[d];
+        G[N + d] = wl * (FLd + sm * JL) + wr * (FRd + sp * JR);
     }
+    const R JL = qL * (L.E + L.p + L.rho * ss * dL);
+    const R JR = qR * (Rs.E + Rs.p + Rs.rho * ss * dR);
+    G[IE] = wl * ((L.E + L.p) * uL + sm * JL) + wr * ((Rs.E + Rs.p) * uR + sp * JR);
 #pragma unroll
     for (int k = 0; k < N - 1; ++k)
         G[IA + k] = (double)wl * (L.al[k] * (double)ss) + (double)wr * (Rs.al[k] * (double)ss);
@@ -931,42 +956,16 @@ __device__ inline void hrm4_pc(const EosDev& e, const St<N, D>& s, double& p, do
 
 // First-order HLLC for the four-equation HRM solved directly, in direction
 // DIR: the solver of Sec. 4.1.1 on (alpha_k rho_k, rho u, E) with the HRM
-// pressure and sound speed of hrm4_pc, the same wave-speed estimates and
-// sign(0) = 0.  The volume-fraction slots of G are zero.
+// pressure and sound speed of hrm4_pc and the same wave-speed estimates.  The
+// volume-fraction slots of G are zero.
 template <int N, int D, int DIR>
-__device__ inline void hllc4(const EosDev& e, const St<N, D>& L, const St<N, D>& Rs, double* G)
+__device__ inline void hllc4(const EosDev& e, St<N, D> L, St<N, D> Rs, double* G)
 {
-    constexpr int IE = N + D, IA = N + D + 1;
-    double pL, cL, pR, cR;
-    hrm4_pc<N, D>(e, L, pL, cL);
-    hrm4_pc<N, D>(e, Rs, pR, cR);
-    const double uL = L.u[DIR], uR = Rs.u[DIR];
-    const double ub = 0.5 * (uL + uR), cb = 0.5 * (cL + cR);
-    const double sL = fmin(ub - cb, uL - cL);
-    const double sR = fmax(ub + cb, uR + cR);
-    const double dL = sL - uL, dR = sR - uR;
-    const double ss = div_rn(pR - pL + L.rho * uL * dL - Rs.rho * uR * dR, L.rho * dL - Rs.rho * dR);
-    const double sg = ss > 0.0 ? 1.0 : (ss < 0.0 ? -1.0 : 0.0);
-    const double wl = 0.5 * (1.0 + sg), wr = 0.5 * (1.0 - sg);
-    const double sm = fmin(0.0, sL), sp = fmax(0.0, sR);
-    const double chiL = div_rn(dL, sL - ss), chiR = div_rn(dR, sR - ss);
+    hrm4_pc<N, D>(e, L, L.p, L.c);
+    hrm4_pc<N, D>(e, Rs, Rs.p, Rs.c);
+    hllc<N, D, DIR>(L, Rs, G);
 #pragma unroll
-    for (int k = 0; k < N; ++k)
-        G[k] = wl * (L.ar[k] * uL + sm * (chiL * L.ar[k] - L.ar[k])) +
-               wr * (Rs.ar[k] * uR + sp * (chiR * Rs.ar[k] - Rs.ar[k]));
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        const double FLd = L.mom[d] * uL + (d == DIR ? pL : 0.0);
-        const double FRd = Rs.mom[d] * uR + (d == DIR ? pR : 0.0);
-        const double WsL = d == DIR ? chiL * L.rho * ss : chiL * L.rho * L.u[d];
-        const double WsR = d == DIR ? chiR * Rs.rho * ss : chiR * Rs.rho * Rs.u[d];
-        G[N + d] = wl * (FLd + sm * (WsL - L.mom[d])) + wr * (FRd + sp * (WsR - Rs.mom[d]));
-    }
-    const double EsL = chiL * (L.E + (ss - uL) * (L.rho * ss + div_rn(pL, dL)));
-    const double EsR = chiR * (Rs.E + (ss - uR) * (Rs.rho * ss + div_rn(pR, dR)));
-    G[IE] = wl * ((L.E + pL) * uL + sm * (EsL - L.E)) + wr * ((Rs.E + pR) * uR + sp * (EsR - Rs.E));
-#pragma unroll
-    for (int k = 0; k < N - 1; ++k) G[IA + k] = 0.0;
+    for (int k = 0; k < N - 1; ++k) G[N + D + 1 + k] = 0.0;
 }
 
 }  // namespace hrm

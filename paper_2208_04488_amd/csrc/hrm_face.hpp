@@ -166,7 +166,7 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
     // limiter when it has to act, so it is formed on demand
     auto first_order = [&](const St<N, D>& L, const St<N, D>& Rn, double* Glo, double* Glo_p) {
         const St<N, D, R> Lr = convert<N, D, R>(L), Rr = convert<N, D, R>(Rn);
-        const double ss = hllc<N, D, DIR, R>(Lr, Rr, Glo);
+        const double ss = hllc<N, D, DIR>(Lr, Rr, Glo);
 #pragma unroll
         for (int k = 0; k < N - 1; ++k) {
             Glo_p[k] = Glo[IA + k] - ss * Rr.al[k];
@@ -272,7 +272,7 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
 
     // midpoint flux and velocity from HLLC on the interpolated states
     double Gt[M];
-    const R ut = hllc<N, D, DIR, R>(VL, VR, Gt);
+    const R ut = hllc<N, D, DIR>(VL, VR, Gt);
 
     // shock sensor (Sec. 4.3.1) on mixture density and pressure, in double in
     // both variants: C_s = 1e12 turns float rounding of p at a contact into
