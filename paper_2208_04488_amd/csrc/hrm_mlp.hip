@@ -4,9 +4,10 @@
 // reduction and the Adam update.  Declarations and semantics: include/hrm.h.
 //
 // The network and the interpolant are described in hrm_mlp.hpp.  Training
-// runs in float32 on the vector ALUs (the matrix-core evaluation in bfloat16
-// is for inference inside the solver): a minibatch has at most a few hundred
-// thousand samples and 1347 parameters, far from any roofline that matters.
+// runs in float32: the layers and the outer products of the gradient on the
+// matrix cores (float32 MFMA, whose products and sums are float32; the
+// bfloat16 evaluation is for inference inside the solver), the weights of the
+// interpolant on the vector ALUs.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -19,7 +20,7 @@
 
 namespace hrm {
 
-constexpr int TR_BLOCK = 64;               // samples per workgroup (one wave)
+constexpr int TR_BLOCK = 64;               // samples per workgroup (four waves of 16)
 constexpr int TR_PARTIAL = MLP_NPARAM + 1;  // gradient entries + loss
 
 // ---------------------------------------------------------------- extraction
@@ -185,132 +186,176 @@ struct GradArgs {
     float* partial;  // gridDim.x x TR_PARTIAL
 };
 
-__global__ void __launch_bounds__(TR_BLOCK) k_mlp_grad(const GradArgs A)
-{
-    __shared__ float sP[MLP_NPARAM];
-    __shared__ float sx[TR_BLOCK][5], sh1[TR_BLOCK][33], sdh1[TR_BLOCK][33], sh2[TR_BLOCK][33],
-        sdh2[TR_BLOCK][33], sdz[TR_BLOCK][3], sl[TR_BLOCK];
-    const int t = threadIdx.x;
-    for (int i = t; i < MLP_NPARAM; i += TR_BLOCK) sP[i] = A.P[i];
-    __syncthreads();
-    const float* W1 = sP + MLP_OFF_W1;
-    const float* b1 = sP + MLP_OFF_B1;
-    const float* W2 = sP + MLP_OFF_W2;
-    const float* b2 = sP + MLP_OFF_B2;
-    const float* W3 = sP + MLP_OFF_W3;
-    const float* b3 = sP + MLP_OFF_B3;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-    const long long k = (long long)blockIdx.x * TR_BLOCK + t;
+// One workgroup takes 64 samples, one wave 16 of them as the columns of
+// 16x16x4 MFMAs (lane l: column l % 16; K entry, or rows 4 g .. 4 g + 3 of the
+// accumulator, by g = l / 16).  A layer's accumulator rows are the next
+// layer's K entries after a renumbering of the units, folded into the A
+// operands: accumulator v of row tile t holds unit 16 t + 4 g + v, and the
+// K step (t, v) of the next layer takes it from the same register.  The
+// weights are read from memory in operand order (5 KB, cached), so the forward
+// and backward passes use no LDS; only the outer products, whose K runs over
+// the samples, go through it, with every wave summing one quarter of them over
+// all 64.  A minibatch of 16 384 is 256 workgroups, one wave per SIMD, and
+// bound by that wave's chain of operations: 35.7 us with one wave per
+// workgroup and the products on the vector ALUs, 8.5 us this way.
+__global__ void __launch_bounds__(4 * TR_BLOCK) k_mlp_grad(const GradArgs A)
+{
+    // activations of the 64 samples in unit tiles of 16: [tile][sample][unit]
+    __shared__ __align__(16) float sh1[2][TR_BLOCK][16], sdh1[2][TR_BLOCK][16], sh2[2][TR_BLOCK][16],
+        sdh2[2][TR_BLOCK][16], sx[TR_BLOCK][16], sdz[TR_BLOCK][16];
+    __shared__ float sb[4][36];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int c = lane & 15, g = lane >> 4;
+    const float* W1 = A.P + MLP_OFF_W1;
+    const float* b1 = A.P + MLP_OFF_B1;
+    const float* W2 = A.P + MLP_OFF_W2;
+    const float* b2 = A.P + MLP_OFF_B2;
+    const float* W3 = A.P + MLP_OFF_W3;
+    const float* b3 = A.P + MLP_OFF_B3;
+    auto mfma = [](float a, float b, f32x4 d) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, d, 0, 0, 0); };
+
+    const long long k = (long long)blockIdx.x * TR_BLOCK + 16 * wv + c;
     const bool on = k < A.count;
     float x[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f}, tt = 0.0f;
     if (on) {
-        const long long idx = (A.first + k * A.stride) % A.nsamp;
+        long long idx = A.first + k * A.stride;
+        if (idx >= A.nsamp) idx -= A.nsamp;
+        if (idx >= A.nsamp) idx %= A.nsamp;
 #pragma unroll
         for (int j = 0; j < 5; ++j) x[j] = A.X[idx * 8 + j];
         tt = A.Tt[idx];
     }
-    // forward
-    float h1[32], h2[32];
+    // forward: layer 1 has K = (x_0..x_4, 1, 0, 0), b1 the weight of the 1
+    const float xa = g == 0 ? x[0] : (g == 1 ? x[1] : (g == 2 ? x[2] : x[3]));
+    const float xb = g == 0 ? x[4] : (g == 1 ? 1.0f : 0.0f);
+    f32x4 h1[2], h2[2];
 #pragma unroll
-    for (int h = 0; h < 32; ++h) {
-        float a = b1[h];
+    for (int t = 0; t < 2; ++t) {
+        const int u = 16 * t + c;
+        const float wb = g == 0 ? W1[4 * 32 + u] : (g == 1 ? b1[u] : 0.0f);
+        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        acc = mfma(W1[g * 32 + u], xa, acc);
+        acc = mfma(wb, xb, acc);
 #pragma unroll
-        for (int j = 0; j < 5; ++j) a += x[j] * W1[j * 32 + h];
-        h1[h] = fmaxf(a, 0.0f);
+        for (int v = 0; v < 4; ++v) h1[t][v] = fmaxf(acc[v], 0.0f);
     }
 #pragma unroll
-    for (int h = 0; h < 32; ++h) {
-        float a = b2[h];
+    for (int t = 0; t < 2; ++t) {
+        f32x4 acc;
 #pragma unroll
-        for (int g = 0; g < 32; ++g) a += h1[g] * W2[g * 32 + h];
-        h2[h] = fmaxf(a, 0.0f);
+        for (int v = 0; v < 4; ++v) acc[v] = b2[16 * t + 4 * g + v];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            acc = mfma(W2[(16 * (q >> 2) + 4 * g + (q & 3)) * 32 + 16 * t + c], h1[q >> 2][q & 3], acc);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) h2[t][v] = fmaxf(acc[v], 0.0f);
     }
-    float z[3];
+    // logits: rows 4 g + k hold logit k (k < 3), so every lane of a column has them
+    f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        float a = b3[c];
+    for (int q = 0; q < 8; ++q)
+        z = mfma((c & 3) < 3 ? W3[(16 * (q >> 2) + 4 * g + (q & 3)) * 3 + (c & 3)] : 0.0f, h2[q >> 2][q & 3], z);
+    // weights: the classical ones of x rescaled by e^{tanh z_k}.  The
+    // indicators and the differences of the candidates are second and third
+    // differences of x, small against x in a smooth stencil: formed in double
+    const double x0d = x[0], x1d = x[1], x2d = x[2], x3d = x[3], x4d = x[4];
+    const double e1 = x0d - 2.0 * x1d + x2d, e2 = x1d - 2.0 * x2d + x3d, e3 = x2d - 2.0 * x3d + x4d;
+    const double s0 = x0d - 4.0 * x1d + 3.0 * x2d, s1 = x1d - x3d, s2 = 3.0 * x2d - 4.0 * x3d + x4d;
+    const float bt[3] = {(float)(13.0 / 12.0 * e1 * e1 + 0.25 * s0 * s0),
+                         (float)(13.0 / 12.0 * e2 * e2 + 0.25 * s1 * s1),
+                         (float)(13.0 / 12.0 * e3 * e3 + 0.25 * s2 * s2)};
+    float th[3], a[3];
 #pragma unroll
-        for (int h = 0; h < 32; ++h) a += h2[h] * W3[h * 3 + c];
-        z[c] = a;
-    }
-    // weights: the classical ones of x rescaled by e^{tanh z_k}
-    float bt[3], th[3];
-    mlp_beta(x, bt);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) th[c] = tanhf(z[c]);
+    for (int q = 0; q < 3; ++q) th[q] = tanhf(z[q] + b3[q]);
     const float my = fmaxf(th[0], fmaxf(th[1], th[2]));
     const float dk[3] = {0.0625f, 0.625f, 0.3125f};
-    float a[3];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const float q = MLP_EPS + bt[c];
-        a[c] = dk[c] * expf(th[c] - my) / (q * q);
+    for (int q = 0; q < 3; ++q) {
+        const float e = MLP_EPS + bt[q];
+        a[q] = dk[q] * expf(th[q] - my) / (e * e);
     }
     const float ie = 1.0f / (a[0] + a[1] + a[2]);
     const float w[3] = {a[0] * ie, a[1] * ie, a[2] * ie};
-    const float S[3] = {(3.0f * x[0] - 10.0f * x[1] + 15.0f * x[2]) * 0.125f,
-                        (-x[1] + 6.0f * x[2] + 3.0f * x[3]) * 0.125f,
-                        (3.0f * x[2] + 6.0f * x[3] - x[4]) * 0.125f};
-    const float res = w[0] * S[0] + w[1] * S[1] + w[2] * S[2] - tt;
-    // backward of the mean squared residual over the minibatch
+    // S_l - S_c and S_r - S_c; the value is S_c + w_l (S_l - S_c) + w_r (S_r - S_c)
+    const double dl = 0.375 * (e1 - e2), dr = 0.125 * (e2 - e3);
+    const float d01 = (float)dl, d21 = (float)dr, d02 = (float)(dl - dr);
+    const float sc = (float)(0.125 * (6.0 * x2d + 3.0 * x3d - x1d));
+    const float res = (sc - tt) + (w[0] * d01 + w[2] * d21);
+    // backward of the mean squared residual over the minibatch:
+    // dL/dy_q = dy w_q sum_k w_k (S_q - S_k), y = tanh z
     const float dy = on ? 2.0f * res / (float)A.count : 0.0f;
-    const float dw[3] = {dy * S[0], dy * S[1], dy * S[2]};
-    const float wdw = w[0] * dw[0] + w[1] * dw[1] + w[2] * dw[2];
     float dz[3];
+    dz[0] = w[0] * (w[1] * d01 + w[2] * d02);
+    dz[1] = -w[1] * (w[0] * d01 + w[2] * d21);
+    dz[2] = w[2] * (w[1] * d21 - w[0] * d02);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) dz[c] = w[c] * (dw[c] - wdw) * (1.0f - th[c] * th[c]);
-    float dh2[32], dh1[32];
+    for (int q = 0; q < 3; ++q) dz[q] *= dy * (1.0f - th[q] * th[q]);
+    f32x4 dh2[2], dh1[2];
+    const float dzk = g == 0 ? dz[0] : (g == 1 ? dz[1] : (g == 2 ? dz[2] : 0.0f));
 #pragma unroll
-    for (int h = 0; h < 32; ++h) {
-        const float a = W3[h * 3 + 0] * dz[0] + W3[h * 3 + 1] * dz[1] + W3[h * 3 + 2] * dz[2];
-        dh2[h] = h2[h] > 0.0f ? a : 0.0f;
+    for (int t = 0; t < 2; ++t) {
+        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        acc = mfma(g < 3 ? W3[(16 * t + c) * 3 + g] : 0.0f, dzk, acc);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) dh2[t][v] = h2[t][v] > 0.0f ? acc[v] : 0.0f;
     }
 #pragma unroll
-    for (int g = 0; g < 32; ++g) {
-        float a = 0.0f;
+    for (int t = 0; t < 2; ++t) {
+        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int h = 0; h < 32; ++h) a += W2[g * 32 + h] * dh2[h];
-        dh1[g] = h1[g] > 0.0f ? a : 0.0f;
+        for (int q = 0; q < 8; ++q)
+            acc = mfma(W2[(16 * t + c) * 32 + 16 * (q >> 2) + 4 * g + (q & 3)], dh2[q >> 2][q & 3], acc);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) dh1[t][v] = h1[t][v] > 0.0f ? acc[v] : 0.0f;
     }
-    // stage the activations and sum the outer products over the samples
+    // the outer products: rows and columns of 16 units, K over the 64 samples
+    const int smp = 16 * wv + c;
 #pragma unroll
-    for (int j = 0; j < 5; ++j) sx[t][j] = x[j];
-#pragma unroll
-    for (int h = 0; h < 32; ++h) {
-        sh1[t][h] = h1[h];
-        sdh1[t][h] = dh1[h];
-        sh2[t][h] = h2[h];
-        sdh2[t][h] = dh2[h];
+    for (int t = 0; t < 2; ++t) {
+        *(f32x4*)&sh1[t][smp][4 * g] = h1[t];
+        *(f32x4*)&sh2[t][smp][4 * g] = h2[t];
+        *(f32x4*)&sdh1[t][smp][4 * g] = dh1[t];
+        *(f32x4*)&sdh2[t][smp][4 * g] = dh2[t];
     }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) sdz[t][c] = dz[c];
-    sl[t] = on ? res * res : 0.0f;
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    const f32x4 x0 = {x[0], x[1], x[2], x[3]}, x1 = {x[4], 1.0f, 0.0f, 0.0f};
+    const f32x4 zl = {dz[0], dz[1], dz[2], on ? res * res : 0.0f};
+    *(f32x4*)&sx[smp][4 * g] = g == 0 ? x0 : (g == 1 ? x1 : zero);
+    *(f32x4*)&sdz[smp][4 * g] = g == 0 ? zl : zero;
     __syncthreads();
+    auto outer = [&](const float (*a)[16], const float (*b)[16]) {
+        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int q = 0; q < TR_BLOCK / 4; ++q) acc = mfma(a[4 * q + g][c], b[4 * q + g][c], acc);
+        return acc;
+    };
     float* out = A.partial + (size_t)blockIdx.x * TR_PARTIAL;
-    for (int p = t; p < TR_PARTIAL; p += TR_BLOCK) {
+    const int ti = wv >> 1, tj = wv & 1;
+    const f32x4 gW2 = outer(sh1[ti], sdh2[tj]);
+    // waves 0 and 1: (x, 1) x dh1, the gradient of W1 and b1; waves 2 and 3: h2 x dz
+    const f32x4 gs = wv < 2 ? outer(sx, sdh1[wv]) : outer(sh2[wv - 2], sdz);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int i = 4 * g + v;
+        out[MLP_OFF_W2 + (16 * ti + i) * 32 + 16 * tj + c] = gW2[v];
+        if (wv < 2 && i < 6) out[(i < 5 ? MLP_OFF_W1 + i * 32 : MLP_OFF_B1) + 16 * wv + c] = gs[v];
+        if (wv >= 2 && c < 3) out[MLP_OFF_W3 + (16 * (wv - 2) + i) * 3 + c] = gs[v];
+    }
+    // plain sums over the samples: dh2 (b2), dz (b3), the squared residual;
+    // every wave a quarter of them, then the four quarters in order
+    if (lane < 36) {
+        const float* col = lane < 32 ? &sdh2[lane >> 4][16 * wv][lane & 15] : &sdz[16 * wv][lane - 32];
         float acc = 0.0f;
-        if (p < MLP_OFF_B1) {
-            const int j = p / 32, h = p % 32;
-            for (int s = 0; s < TR_BLOCK; ++s) acc += sx[s][j] * sdh1[s][h];
-        } else if (p < MLP_OFF_W2) {
-            const int h = p - MLP_OFF_B1;
-            for (int s = 0; s < TR_BLOCK; ++s) acc += sdh1[s][h];
-        } else if (p < MLP_OFF_B2) {
-            const int g = (p - MLP_OFF_W2) / 32, h = (p - MLP_OFF_W2) % 32;
-            for (int s = 0; s < TR_BLOCK; ++s) acc += sh1[s][g] * sdh2[s][h];
-        } else if (p < MLP_OFF_W3) {
-            const int h = p - MLP_OFF_B2;
-            for (int s = 0; s < TR_BLOCK; ++s) acc += sdh2[s][h];
-        } else if (p < MLP_OFF_B3) {
-            const int h = (p - MLP_OFF_W3) / 3, c = (p - MLP_OFF_W3) % 3;
-            for (int s = 0; s < TR_BLOCK; ++s) acc += sh2[s][h] * sdz[s][c];
-        } else if (p < MLP_NPARAM) {
-            const int c = p - MLP_OFF_B3;
-            for (int s = 0; s < TR_BLOCK; ++s) acc += sdz[s][c];
-        } else {
-            for (int s = 0; s < TR_BLOCK; ++s) acc += sl[s];
-        }
-        out[p] = acc;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc += col[16 * q];
+        sb[wv][lane] = acc;
+    }
+    __syncthreads();
+    if (threadIdx.x < 36) {
+        const int i = threadIdx.x;
+        out[i < 32 ? MLP_OFF_B2 + i : MLP_OFF_B3 + (i - 32)] = ((sb[0][i] + sb[1][i]) + sb[2][i]) + sb[3][i];
     }
 }
 
@@ -495,7 +540,7 @@ int grad_launch(const float* d_params, const float* d_X, const float* d_T, long 
     A.count = count;
     A.partial = work;
     const int nblk = (count + hrm::TR_BLOCK - 1) / hrm::TR_BLOCK;
-    hipLaunchKernelGGL(hrm::k_mlp_grad, dim3(nblk), dim3(hrm::TR_BLOCK), 0, s, A);
+    hipLaunchKernelGGL(hrm::k_mlp_grad, dim3(nblk), dim3(4 * hrm::TR_BLOCK), 0, s, A);
     hipLaunchKernelGGL(hrm::k_mlp_reduce, dim3((hrm::TR_PARTIAL + hrm::RD_P - 1) / hrm::RD_P),
                        dim3(hrm::RD_P * hrm::RD_S), 0, s, work, nblk, count, d_grad, d_loss);
     return hipGetLastError() == hipSuccess ? HRM_OK : HRM_EDEVICE;

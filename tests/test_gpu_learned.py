@@ -141,6 +141,37 @@ def test_training_gradient_matches_numpy_oracle(H, M):
         assert err <= 5e-6 and lerr <= 3e-7  # measured up to 6.8e-7 and 3.2e-8
 
 
+@pytest.mark.parametrize("count", [1, 15, 16, 17, 63, 64, 65, 300])
+def test_training_gradient_partial_workgroups(H, M, count):
+    """Minibatches that leave columns, waves or workgroups partly filled, with
+    sample indices that wrap more than once, against the NumPy oracle.  A
+    residual of order one carries a few float32 roundings of values up to 4
+    (4e-6), relative to itself where it is smaller."""
+    import torch
+    rng = np.random.default_rng(40 + count)
+    n, first, stride = 37, 30, 11
+    X64, _ = M.normalise(stencils(rng, n))
+    X32 = np.zeros((n, 8), dtype=np.float32)
+    X32[:, :5] = X64
+    T32 = rng.uniform(-1.5, 1.5, size=n).astype(np.float32)
+    p = rand_params(M, 7, 1.0)
+    p[160:192] = rng.normal(size=32) * 0.1
+    p[1216:1248] = rng.normal(size=32) * 0.1
+    dev = torch.device("cuda")
+    tp, tX, tT = (torch.from_numpy(a).to(dev) for a in (p, X32, T32))
+    g = torch.zeros(M.NPARAM, dtype=torch.float32, device=dev)
+    loss = torch.zeros(1, dtype=torch.float32, device=dev)
+    work = torch.zeros(H.hrm_mlp_grad_workspace(count), dtype=torch.float32, device=dev)
+    H.hrm_mlp_grad(tp, tX, tT, first, stride, count, g, loss, work)
+    torch.cuda.synchronize()
+    idx = (first + np.arange(count) * stride) % n
+    Xd, Td, pd = X32[idx, :5].astype(np.float64), T32[idx].astype(np.float64), p.astype(np.float64)
+    gref, lref = M.grad(pd, Xd, Td), M.loss(pd, Xd, Td)
+    small = max(1.0, 1.0 / np.sqrt(lref))
+    assert np.abs(g.cpu().numpy() - gref).max() <= 5e-6 * small * np.abs(gref).max()
+    assert abs(loss.item() - lref) <= 8e-6 * small * lref
+
+
 def test_minibatch_indexing(H, M):
     """Samples (first + k stride) mod n: the gradient of a strided minibatch
     equals that of the same samples gathered on the host."""
