@@ -10,12 +10,13 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libhrm.so")
-SOURCES = ["hrm.hip", "hrm_batch.hip", "hrm_mlp.hip"]
-# per-source flags: the persistent batch kernel wraps the face arithmetic in
+SOURCES = ["hrm.hip", "hrm_line.hip", "hrm_batch.hip", "hrm_mlp.hip"]
+# per-source flags: the batch and line kernels wrap the face arithmetic in
 # problem / step / stage / tile loops; machine-level loop-invariant code motion
 # would lift dozens of FP64 constant materialisations out of them and keep
 # them in vector registers for the whole launch (spills at two waves/SIMD)
-SOURCE_FLAGS = {"hrm_batch.hip": ["-mllvm", "-disable-machine-licm"]}
+SOURCE_FLAGS = {"hrm_batch.hip": ["-mllvm", "-disable-machine-licm"],
+                "hrm_line.hip": ["-mllvm", "-disable-machine-licm"]}
 ARCH = "gfx950"
 
 # -packed-fp32-ops: the compiler emits no packed FP32 (v_pk_*_f32) instructions

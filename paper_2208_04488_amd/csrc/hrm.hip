@@ -18,6 +18,7 @@
 //                     hrm_max_wavespeed), then k_reduce_max / k_reduce_dt
 //                     (which clears the slots the sweep folds into).
 //   k_dt              the time step and lambda_d on the device.
+// Lines of up to LINE_CELLS cells advance in one workgroup (hrm_line.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -28,6 +29,7 @@
 
 #include "hrm.h"
 #include "hrm_face.hpp"
+#include "hrm_line.hpp"
 
 namespace hrm {
 
@@ -114,9 +116,12 @@ constexpr bool sweep_slim()
 template <int D, int DIR, typename R, int WT>
 constexpr int sweep_waves()
 {
-    return sizeof(R) == sizeof(double) && WT == 0 && D >= 2 ? 4 : 3;
+    return WT == 2 || (sizeof(R) == sizeof(double) && WT == 0 && D >= 2) ? 4 : 3;
 }
 
+// WT: 0 App. C weights, 1 learned weights, 2 the first-order schemes in double
+// (the five-equation one and the four-equation HRM), a small kernel that
+// stages one node beyond each end instead of three.
 // WS: the launch is a stage update that also folds the wavespeed maxima of
 // its output into A.wpart; a separate instantiation, so that the other
 // launches keep their register allocation
@@ -127,7 +132,8 @@ __global__ void __launch_bounds__(BS* BA, (sweep_waves<D, DIR, R, WT>())) k_swee
     using F = NodeFields<N, D, SLIM>;
     constexpr int M = 2 * N + D, IA = N + D + 1;
     constexpr int NA = N > 1 ? N - 1 : 1;
-    constexpr int LN = BS + 5;
+    constexpr int H = WT == 2 ? 1 : 3;  // nodes staged beyond the first and last face's cells
+    constexpr int LN = BS - 1 + 2 * H;
     constexpr int FS = BA * LN;
     constexpr int NS = DIR == 0 ? 1 : BA;
     static_assert((BS * BA) % 64 == 0, "whole waves");
@@ -161,41 +167,57 @@ __global__ void __launch_bounds__(BS* BA, (sweep_waves<D, DIR, R, WT>())) k_swee
     const long long nc = A.ncell;
     auto base = [](int a, int l) { return DIR == 0 ? a * LN + l : l * BA + a; };
 
-    // stage the node tile (sweep index c0-3 .. c0+BS+1) with its primitives.
+    // stage the node tile (sweep index c0-H .. c0+BS-2+H) with its primitives.
     // The staging waves run at raised priority, so that a workgroup starting
     // beside others still computing faces gets its loads out first (1024 x
     // 512 step -2.4 %, 256^3 FP64 -1 %, FP32 -2.6 %; raising it also around
-    // the stage update's loads measured slower)
+    // the stage update's loads measured slower).  A tile has a few more nodes
+    // than threads: the loads of a thread's second node are issued with those
+    // of its first, so that the waves that have one wait for memory once.
     __builtin_amdgcn_s_setprio(3);
-    for (int q = tid; q < LN * BA; q += BS * BA) {
-        const int l = DIR == 0 ? q % LN : q / BA;
-        const int a = DIR == 0 ? q / LN : q % BA;
-        const int gi = c0 - 3 + l;
-        const int ca = min(abase + a, na - 1);
-        const double* src = A.Ws;
-        long long idx, stride = nc;
-        if ((gi < 0 && A.bclo == BC_DIRICHLET) || (gi >= nsw && A.bchi == BC_DIRICHLET)) {
-            // Dirichlet: every ghost node takes the boundary state of its line
-            src = gi < 0 ? A.blo : A.bhi;
-            idx = ca + (long long)na * other;
-            stride = (long long)na * A.n[odim];
-        } else {
-            idx = map_bc(gi, nsw, A.bclo, A.bchi) * st[DIR] + ca * st[adim] + other * st[odim];
+    constexpr int NQ = LN * BA, T = BS * BA, IT = (NQ + T - 1) / T;
+    {
+        double W[IT][M];
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int q = tid + it * T;
+            if ((it + 1) * T > NQ && q >= NQ) continue;
+            const int l = DIR == 0 ? q % LN : q / BA;
+            const int a = DIR == 0 ? q / LN : q % BA;
+            const int gi = c0 - H + l;
+            const int ca = min(abase + a, na - 1);
+            const double* src = A.Ws;
+            long long idx, stride = nc;
+            if ((gi < 0 && A.bclo == BC_DIRICHLET) || (gi >= nsw && A.bchi == BC_DIRICHLET)) {
+                // Dirichlet: every ghost node takes the boundary state of its line
+                src = gi < 0 ? A.blo : A.bhi;
+                idx = ca + (long long)na * other;
+                stride = (long long)na * A.n[odim];
+            } else {
+                idx = map_bc(gi, nsw, A.bclo, A.bchi) * st[DIR] + ca * st[adim] + other * st[odim];
+            }
+#pragma unroll
+            for (int c = 0; c < M; ++c) W[it][c] = src[c * stride + idx];
         }
-        double W[M];
+        const EosDev e = kload<EosDev>(kernel_args() + offsetof(SweepArgs, e));
 #pragma unroll
-        for (int c = 0; c < M; ++c) W[c] = src[c * stride + idx];
-        St<N, D> s;
-        state_from_W<N, D>(A.e, W, s);
-        const int b = base(a, l);
+        for (int it = 0; it < IT; ++it) {
+            const int q = tid + it * T;
+            if ((it + 1) * T > NQ && q >= NQ) continue;
+            St<N, D> s;
+            state_from_W<N, D>(e, W[it], s);
+            if constexpr (WT == 2)
+                if (A.P.flags & F_FOUR_EQ) hrm4_pc<N, D>(e, s, s.p, s.c);
+            const int b = base(DIR == 0 ? q / LN : q % BA, DIR == 0 ? q % LN : q / BA);
 #pragma unroll
-        for (int c = 0; c < M; ++c) lds[c * FS + b] = W[c];
+            for (int c = 0; c < M; ++c) lds[c * FS + b] = W[it][c];
 #pragma unroll
-        for (int d = 0; d < D; ++d) lds[(F::U + d) * FS + b] = s.u[d];
-        lds[F::P * FS + b] = s.p;
-        if constexpr (!SLIM) lds[F::RHO * FS + b] = s.rho;
-        lds[F::C * FS + b] = s.c;
-        lds[F::RC2 * FS + b] = s.rc2;
+            for (int d = 0; d < D; ++d) lds[(F::U + d) * FS + b] = s.u[d];
+            lds[F::P * FS + b] = s.p;
+            if constexpr (!SLIM) lds[F::RHO * FS + b] = s.rho;
+            lds[F::C * FS + b] = s.c;
+            lds[F::RC2 * FS + b] = s.rc2;
+        }
     }
     __builtin_amdgcn_s_setprio(0);
     __syncthreads();
@@ -212,8 +234,10 @@ __global__ void __launch_bounds__(BS* BA, (sweep_waves<D, DIR, R, WT>())) k_swee
     if (live) {
         unsigned lc = 0;
         const KArg ka = kernel_args();
-        face_flux<N, D, DIR, NS, FS, R, WT, true, SLIM>(
-            lds + base(ta, ts), ka + offsetof(SweepArgs, e), ka + offsetof(SweepArgs, P), A.slot[1 + DIR], G, Gp, lc);
+        // the first-order float scheme is the general kernel's
+        constexpr int LOW = WT == 2 ? 2 : (sizeof(R) == sizeof(double) ? 0 : 1);
+        face_flux<N, D, DIR, NS, FS, R, WT == 1 ? 1 : 0, LOW, SLIM>(
+            lds + base(ta, ts + H - 3), ka + offsetof(SweepArgs, e), ka + offsetof(SweepArgs, P), A.slot[1 + DIR], G, Gp, lc);
         // face c0+ts is counted once: the last face of a tile is the first
         // face of the next tile unless it is the boundary face nsw
         const int f = c0 + ts;
@@ -283,19 +307,22 @@ __global__ void __launch_bounds__(BS* BA, (sweep_waves<D, DIR, R, WT>())) k_swee
                     const double Lc = D > 1 ? A.rhs[c * nc + cell] + L[c] : L[c];
                     w[c] = A.a * A.Wn[c * nc + cell] + A.b * (A.Ws[c * nc + cell] + dt * Lc);
                 }
-                if (A.relax && !relax_cell<N, D>(A.e, w)) cnt += cnt_one(C_RELAX_BAD);
+                if (A.relax && !relax_cell<N, D>(kload<EosDev>(kernel_args() + offsetof(SweepArgs, e)), w))
+                    cnt += cnt_one(C_RELAX_BAD);
             }
 #pragma unroll
             for (int c = 0; c < M; ++c) A.Wout[c * nc + cell] = w[c];
             if constexpr (WS) {
                 // Sec. 4.1.2: |u_d| + c of the new state, for the next time step
+                const EosDev e = kload<EosDev>(kernel_args() + offsetof(SweepArgs, e));
                 St<N, D> s;
-                state_from_W<N, D>(A.e, w, s);
+                state_from_W<N, D>(e, w, s);
                 double cs = s.c;
-                if (A.P.flags & F_FOUR_EQ) {
-                    double p;
-                    hrm4_pc<N, D>(A.e, s, p, cs);
-                }
+                if constexpr (WT == 2)
+                    if (A.P.flags & F_FOUR_EQ) {
+                        double p;
+                        hrm4_pc<N, D>(e, s, p, cs);
+                    }
 #pragma unroll
                 for (int d = 0; d < D; ++d) wmax[d] = fabs(s.u[d]) + cs;
             }
@@ -432,29 +459,6 @@ __global__ void __launch_bounds__(RT) k_reduce_max(const double* part, int nb, d
     if (threadIdx.x == 0)
 #pragma unroll
         for (int d = 0; d < D; ++d) out[d] = m[d];
-}
-
-struct DtArgs {
-    int D;
-    double dx[3];
-    double cfl, dt_fixed, t_end;
-};
-
-// Sec. 4.1.2: tau_d = maxs_d / dx_d, dt = CFL / sum tau (or the fixed step),
-// lambda_d = dt / (sigma_d dx_d); clipped to t_end with the device time slot[4]
-__device__ inline void dt_from_max(const double* maxs, const DtArgs& a, double* slot)
-{
-    double tau[3] = {0.0, 0.0, 0.0}, ts = 0.0;
-    for (int d = 0; d < a.D; ++d) {
-        tau[d] = maxs[d] / a.dx[d];
-        ts += tau[d];
-    }
-    double dt = a.dt_fixed > 0.0 ? a.dt_fixed : a.cfl / ts;
-    const double t = slot[4];
-    if (a.t_end > 0.0 && t + dt > a.t_end) dt = fmax(a.t_end - t, 0.0);
-    slot[0] = dt;
-    for (int d = 0; d < 3; ++d) slot[1 + d] = d < a.D ? dt / ((tau[d] / ts) * a.dx[d]) : 0.0;
-    slot[4] = a.t_end > 0.0 && t + dt >= a.t_end ? a.t_end : t + dt;
 }
 
 __global__ void k_dt(const double* maxs, DtArgs a, double* slot)
@@ -670,6 +674,11 @@ struct Ops {
     template <int DIR, int BS, int BA, bool WS>
     static void launch_kernel(hrm_ctx* c, const hrm::SweepArgs& A, dim3 grd, dim3 blk, hipStream_t s)
     {
+        // first-order schemes: all double except the float five-equation one
+        if ((c->flags & HRM_FOUR_EQ) || ((c->flags & HRM_FIRST_ORDER) && c->precision == HRM_FP64)) {
+            hipLaunchKernelGGL((hrm::k_sweep<N, D, DIR, BS, BA, double, 2, WS>), grd, blk, 0, s, A);
+            return;
+        }
         if constexpr (D <= 2 && !(DIR == 0 && BS == 32)) {
             // learned weights: FP64 face arithmetic, one and two dimensions,
             // on the 64 x 4 x-tile (sweep_tile)
@@ -1201,6 +1210,28 @@ int hrm_advance(hrm_ctx* c, double* d_W, int nsteps, double cfl, double dt_fixed
     if (nsteps == 0) return HRM_OK;
     hipStream_t s = (hipStream_t)stream;
     c->last_stream = s;
+    // a line that one workgroup holds: all steps in one launch (the launch
+    // timers want the sweeps one by one)
+    if (c->D == 1 && !c->timing_mask && c->n[0] <= hrm::line_cells(c->par.flags, c->precision, c->weights)) {
+        if (const int rb = check_boundary(c)) return rb;
+        hrm::LineArgs A;
+        memset(&A, 0, sizeof(A));
+        A.W = d_W;
+        A.slot = d_slot;
+        A.cnt = c->d_cnt;
+        A.n = c->n[0];
+        A.nsteps = nsteps;
+        A.bclo = c->bclo[0];
+        A.bchi = c->bchi[0];
+        A.blo = c->d_bnd[0][0];
+        A.bhi = c->d_bnd[0][1];
+        A.idx = 1.0 / c->dx[0];
+        A.dt = dt_args(c, cfl, dt_fixed, t_end);
+        A.e = c->eos;
+        A.P = c->par;
+        hrm::line_launch(c->N, c->precision, A, s);
+        return check_launch(c, "hrm_advance line");
+    }
     int rc = seed_enqueue(c, d_W, s);
     if (rc != HRM_OK) return rc;
     if ((c->flags & HRM_NO_GRAPH) || c->timing_mask) {

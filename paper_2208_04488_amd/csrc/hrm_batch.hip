@@ -151,7 +151,7 @@ __global__ void __launch_bounds__(BS, 3) k_batch(const BatchArgs A)
                     if (live) {
                         unsigned lc = 0;  // packed counts of this face (cnt_one)
                         const KArg ka = kernel_args();
-                        face_flux<N, D, 0, 1, FS, R, 0, false>(lds + ts, ka + offsetof(BatchArgs, e),
+                        face_flux<N, D, 0, 1, FS, R, 0, 0>(lds + ts, ka + offsetof(BatchArgs, e),
                                                                ka + offsetof(BatchArgs, P), lam, G, Gp, lc);
                         const int f = c0 + ts;  // counted once, as in k_sweep
                         if (f <= n && (ts < BS - 1 || f == n))

@@ -112,15 +112,15 @@ __device__ inline St<N, D, R> convert(const St<N, D, S>& s)
 // Sec. 2 mixture EOS: Gam = 1/(gbar-1) = sum alpha_k/(gamma_k-1),
 // Pi = gbar pbar/(gbar-1) = sum alpha_k gamma_k pinf_k/(gamma_k-1);
 // rho(e - qbar) = Gam p + Pi; rho c^2 = gbar (p + pbar) = p + (p + Pi)/Gam.
-template <int N, typename R>
-__device__ inline void mixture(const EosDev& e, const R* al, R& Gam, R& Pi)
+template <int N>
+__device__ inline void mixture(const EosDev& e, const double* al, double& Gam, double& Pi)
 {
-    Gam = 0;
-    Pi = 0;
+    Gam = al[0] * e.ig1[0];
+    Pi = al[0] * e.gpi1[0];
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-        Gam += al[k] * (R)e.ig1[k];
-        Pi += al[k] * (R)e.gpi1[k];
+    for (int k = 1; k < N; ++k) {
+        Gam = fma(al[k], e.ig1[k], Gam);
+        Pi = fma(al[k], e.gpi1[k], Pi);
     }
 }
 
@@ -163,17 +163,22 @@ __device__ inline double sqrt_rn(double x)
 __device__ inline float div_rn(float a, float b) { return a / b; }
 __device__ inline float sqrt_rn(float x) { return sqrt(x); }
 
-// conservative W[M] -> full state (hot-path step a1)
+// conservative W[M] -> full state (hot-path step a1).  The multiply-adds are
+// written out and no others formed, so that every kernel that takes |u| + c of
+// a cell (the separate pass, the sweep that wrote it, the line) gets the same
+// bits, and with them the same time step.
 template <int N, int D>
 __device__ inline void state_from_W(const EosDev& e, const double* W, St<N, D>& s)
 {
+#pragma clang fp contract(off)
     constexpr int IE = N + D, IA = N + D + 1;
-    double rho = 0.0, rq = 0.0;
+    double rho = W[0], rq = W[0] * e.q[0];
+    s.ar[0] = W[0];
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
+    for (int k = 1; k < N; ++k) {
         s.ar[k] = W[k];
         rho += W[k];
-        rq += W[k] * e.q[k];
+        rq = fma(W[k], e.q[k], rq);
     }
     double asum = 0.0;
 #pragma unroll
@@ -183,20 +188,20 @@ __device__ inline void state_from_W(const EosDev& e, const double* W, St<N, D>& 
     }
     s.al[N - 1] = 1.0 - asum;
     const double irho = rcp_newton(rho);
-    double m2 = 0.0;
+    double m2 = W[N] * W[N];
 #pragma unroll
     for (int d = 0; d < D; ++d) {
         s.mom[d] = W[N + d];
         s.u[d] = W[N + d] * irho;
-        m2 += W[N + d] * W[N + d];
+        if (d > 0) m2 = fma(W[N + d], W[N + d], m2);
     }
     double Gam, Pi;
     mixture<N>(e, s.al, Gam, Pi);
     const double iG = rcp_newton(Gam);
     s.E = W[IE];
-    const double re = W[IE] - 0.5 * m2 * irho - rq;
+    const double re = fma(-0.5 * m2, irho, W[IE]) - rq;
     s.p = (re - Pi) * iG;
-    s.rc2 = s.p + (s.p + Pi) * iG;
+    s.rc2 = fma(s.p + Pi, iG, s.p);
     s.rho = rho;
     const double c2 = s.rc2 * irho;
     s.c = c2 == 0.0 ? 0.0 : sqrt_rn(c2);
@@ -217,7 +222,7 @@ __device__ inline void complete_from_prim(const EosDev& e, St<N, D, R>& s)
     for (int k = 0; k < N - 1; ++k) asum += s.al[k];
     s.al[N - 1] = 1.0 - asum;
     double Gd, Pd;
-    mixture<N, double>(e, s.al, Gd, Pd);
+    mixture<N>(e, s.al, Gd, Pd);
     const R Gam = (R)Gd, Pi = (R)Pd;
     R u2 = 0;
 #pragma unroll
@@ -954,18 +959,27 @@ __device__ inline void hrm4_pc(const EosDev& e, const St<N, D>& s, double& p, do
     c = sqrt_rn(div_rn(p * (re + p) * (SR * p + p1 * S2), rho * (Sv * p * p + re * p1 * S2)));
 }
 
-// First-order HLLC for the four-equation HRM solved directly, in direction
-// DIR: the solver of Sec. 4.1.1 on (alpha_k rho_k, rho u, E) with the HRM
-// pressure and sound speed of hrm4_pc and the same wave-speed estimates.  The
-// volume-fraction slots of G are zero.
-template <int N, int D, int DIR>
-__device__ inline void hllc4(const EosDev& e, St<N, D> L, St<N, D> Rs, double* G)
+struct DtArgs {
+    int D;
+    double dx[3];
+    double cfl, dt_fixed, t_end;
+};
+
+// Sec. 4.1.2: tau_d = maxs_d / dx_d, dt = CFL / sum tau (or the fixed step),
+// lambda_d = dt / (sigma_d dx_d); clipped to t_end with the device time slot[4]
+__device__ inline void dt_from_max(const double* maxs, const DtArgs& a, double* slot)
 {
-    hrm4_pc<N, D>(e, L, L.p, L.c);
-    hrm4_pc<N, D>(e, Rs, Rs.p, Rs.c);
-    hllc<N, D, DIR>(L, Rs, G);
-#pragma unroll
-    for (int k = 0; k < N - 1; ++k) G[N + D + 1 + k] = 0.0;
+    double tau[3] = {0.0, 0.0, 0.0}, ts = 0.0;
+    for (int d = 0; d < a.D; ++d) {
+        tau[d] = maxs[d] / a.dx[d];
+        ts += tau[d];
+    }
+    double dt = a.dt_fixed > 0.0 ? a.dt_fixed : a.cfl / ts;
+    const double t = slot[4];
+    if (a.t_end > 0.0 && t + dt > a.t_end) dt = fmax(a.t_end - t, 0.0);
+    slot[0] = dt;
+    for (int d = 0; d < 3; ++d) slot[1 + d] = d < a.D ? dt / ((tau[d] / ts) * a.dx[d]) : 0.0;
+    slot[4] = a.t_end > 0.0 && t + dt >= a.t_end ? a.t_end : t + dt;
 }
 
 }  // namespace hrm

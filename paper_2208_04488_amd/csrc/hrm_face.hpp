@@ -9,7 +9,8 @@
 namespace hrm {
 
 // LDS node record: the conservative vector W (M slots), then u_d (D),
-// p, rho, c, rho c^2.  The slim record leaves rho out (it is the sum of the
+// p, rho, c, rho c^2 (p and c those of the four-equation HRM where that is
+// solved: once per node here, not once per face and side).  The slim record leaves rho out (it is the sum of the
 // partial densities, formed again where it is read): one field less lets
 // the 3D y- and z-sweeps' 16 x 16 tiles fit four workgroups per CU.
 template <int N, int D, bool SLIM = false>
@@ -128,10 +129,11 @@ __device__ inline double sensor_product(const double* r, const double* p)
 // Output: G = G^{**,-}_{i+1/2} (M slots) and Gp = alpha slots of G^{**,+}.
 // ke and kp: the species table and the parameters in the kernel arguments.
 // R is the face arithmetic type; node data, the flux limiter and the outputs
-// are double.  LOW = false leaves out the first-order and direct-HRM branches
-// (selected by flags) for callers that never take them.  Always inlined:
+// are double.  LOW = 0 leaves out the first-order and direct-HRM branches
+// (selected by flags) for callers that never take them, LOW = 2 leaves out
+// everything else for callers that only take those.  Always inlined:
 // a call would spill the whole face state around it.
-template <int N, int D, int DIR, int NS, int FS, typename R, int WT = 0, bool LOW = true, bool SLIM = false>
+template <int N, int D, int DIR, int NS, int FS, typename R, int WT = 0, int LOW = 1, bool SLIM = false>
 __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, double lam, double* G, double* Gp,
                                           unsigned& cnt)
 {
@@ -174,13 +176,16 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
         }
     };
     const int flags = kload<ParDev>(kp).flags;
-    if (LOW && (flags & F_FIRST_ORDER)) {
+    if (LOW == 2 || (LOW && (flags & F_FIRST_ORDER))) {
         St<N, D> L, Rn;
         node_pair(L, Rn);
         if (flags & F_FOUR_EQ) {
-            hllc4<N, D, DIR>(kload<EosDev>(ke), L, Rn, G);
+            // the four-equation HRM solved directly: the same solver on
+            // (alpha_k rho_k, rho u, E); the node records hold the HRM pressure
+            // and sound speed, and the volume fractions are not evolved
+            hllc<N, D, DIR>(L, Rn, G);
 #pragma unroll
-            for (int k = 0; k < N - 1; ++k) Gp[k] = 0.0;
+            for (int k = 0; k < N - 1; ++k) G[IA + k] = Gp[k] = 0.0;
             return;
         }
         double Glo[M], Glo_p[NA];

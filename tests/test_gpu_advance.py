@@ -268,3 +268,46 @@ def test_advance_zero_steps_and_errors(H):
     with pytest.raises(H.HrmError, match="cfl"):
         s.advance(2, cfl=0.0)
     s.close()
+
+
+# lines one workgroup advances (k_line: up to 511 cells, first order 1023) at the
+# edges of its block sizes, and the first ones beyond
+@pytest.mark.parametrize("n", [1, 2, 3, 63, 64, 255, 256, 511, 512, 1023, 1024])
+@pytest.mark.parametrize("kind", ["open", "periodic", "dirichlet", "three", "fp32", "first", "four_eq"])
+def test_short_line_against_stages(H, n, kind):
+    """Two steps of hrm_advance on a line against the caller's own loop of
+    wavespeed, time step and stages (the sweep kernels).  The arithmetic is the
+    same up to the contraction of multiply-adds, which two relaxed steps carry
+    to 2e-11 as the ensemble's bar has it; in float to float rounding of the
+    fluxes, 2e-6."""
+    import torch
+    flags = H.FUSE_RELAX | {"first": H.FIRST_ORDER, "four_eq": H.FOUR_EQ}.get(kind, 0)
+    prec = H.FP32 if kind == "fp32" else H.FP64
+    base = I.shock_interface(n) if kind == "three" else I.config1(n)
+    bc = {"periodic": (I.PERIODIC, I.PERIODIC), "dirichlet": (I.DIRICHLET, I.TRANSMISSIVE)}.get(kind, (0, 0))
+    prob = I.Problem(base.name, base.eos, 1, base.n, base.dx, [bc], base.W, cfl=0.4)
+    if kind == "dirichlet":
+        prob.boundary = {(0, 0): np.ascontiguousarray(base.W[:, 0, 0, :1])}
+    a, b = (H.Solver(prob, flags=flags, precision=prec) for _ in range(2))
+    a.advance(2, cfl=0.4)
+    for _ in range(2):
+        b.wavespeed()
+        b.compute_dt(0.4)
+        w1 = b.stage(0, b.W, b.W)
+        w2 = b.stage(1, b.W, w1)
+        b.W.copy_(b.stage(2, b.W, w2))
+    torch.cuda.synchronize()
+    da, db = a.diagnostics(), b.diagnostics()
+    got, ref = a.state(), b.state()
+    N, M = prob.N, prob.M
+    scale = np.abs(ref.reshape(M, -1)).max(axis=1)
+    scale[N] = ref[:N].sum(0).max() * b.wavespeed().max()
+    scale[N + 2:] = 1.0
+    err = (np.abs(got - ref).reshape(M, -1).max(axis=1) / scale).max()
+    tol = 2e-6 if kind == "fp32" else 2e-11
+    assert err <= tol
+    assert np.allclose(a.slot[:5].cpu().numpy(), b.slot[:5].cpu().numpy(), rtol=tol, atol=0)
+    if kind != "fp32":
+        assert da == db
+    a.close()
+    b.close()
