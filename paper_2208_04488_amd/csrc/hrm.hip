@@ -47,6 +47,7 @@ struct SweepArgs {
     const double* bhi;
     double* wpart;  // mode 2, non-null: maxima of |u_d| + c of the stage output, block b into slot b % nslot
     unsigned nslot; // a power of two, at most the number of blocks
+    unsigned rnp;   // packed lines: floor(2^32 / (n[0] + 1)), or 0 from 2^32 faces on
     int mode;  // 0: rhs = L_d, 1: rhs += L_d, 2: stage update with rhs + L_d
     int relax;
     int hold;  // mode 2 within a full RK3 step: a step of dt = 0 (the end time reached) leaves W^n as it is
@@ -87,6 +88,28 @@ __device__ inline unsigned long long wave_umax64(unsigned long long v)
     return ((unsigned long long)hi << 32) | lo;
 }
 
+// Packed lines: x-sweeps of 2D and 3D grids whose lines the tiles fit badly.
+// The n + 1 faces of every line follow one another in one sequence, line after
+// line, and a workgroup takes 256 consecutive ones, the last of which is the
+// first of the next workgroup; the cells with both faces in a workgroup are
+// updated there.  Each line's part of a workgroup (at most PACK_SEGS parts)
+// has its own halo nodes in LDS.  A tile per line computes 288 faces for 257
+// where n = 256 and 1088 for 1025 where n = 1024; the sequence computes 258
+// and 1029.
+constexpr int PACK_MIN = 31, PACK_SEGS = 9;
+
+// line of position a in a sequence of lines of b positions, the first of
+// which a block's few hundred positions begin in: a / b, by comparison where
+// they reach no further than the third line
+__device__ inline int part_of(int a, int b)
+{
+    if (b > 150) return (a >= b) + (a >= 2 * b);
+    int q = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
+    q -= q * b > a;
+    q += (q + 1) * b <= a;
+    return q;
+}
+
 // Tile: BS face threads along the sweep direction (BS-1 cells), BA threads
 // across it.  DIR == 0: blockDim = (BS, BA), across = y, blockIdx.z = z.
 // DIR == 1: blockDim = (BA, BS), across = x, blockIdx.z = z.
@@ -103,16 +126,8 @@ __device__ inline unsigned long long wave_umax64(unsigned long long v)
 // face keeps few values past the flux limiter's check, where the
 // workgroups' LDS fits: 1024 x 512 step -1.9 %, 256^3 x-sweep -1.5 %,
 // z-sweep (three arrays read per cell after its barriers) -5 %, y-sweep
-// -2 %.  The 3D y- and z-sweeps' 16 x 16 tiles fit four workgroups per CU
-// only with the slim node record (rho formed again where read, which costs
-// the x-sweep 2 % where its LDS fits anyway).  In float a fourth wave does
-// not pay (256^3 x-sweep +3.5 %).
-template <int D, int DIR, typename R, int WT>
-constexpr bool sweep_slim()
-{
-    return sizeof(R) == sizeof(double) && WT == 0 && D == 3 && DIR >= 1;
-}
-
+// -2 %.  In float a fourth wave does not pay (256^3 x-sweep +3.5 %), and a
+// fifth (96 VGPRs) in 2D makes the 1024 x 512 step 14 % slower.
 template <int D, int DIR, typename R, int WT>
 constexpr int sweep_waves()
 {
@@ -128,13 +143,15 @@ constexpr int sweep_waves()
 template <int N, int D, int DIR, int BS, int BA, typename R, int WT, bool WS = false>
 __global__ void __launch_bounds__(BS* BA, (sweep_waves<D, DIR, R, WT>())) k_sweep(const SweepArgs A)
 {
-    constexpr bool SLIM = sweep_slim<D, DIR, R, WT>();
-    using F = NodeFields<N, D, SLIM>;
+    using F = NodeFields<N, D>;
     constexpr int M = 2 * N + D, IA = N + D + 1;
     constexpr int NA = N > 1 ? N - 1 : 1;
     constexpr int H = WT == 2 ? 1 : 3;  // nodes staged beyond the first and last face's cells
+    // packed lines (x-sweeps in 2D and 3D, see the tiles above)
+    constexpr bool PK = D >= 2 && DIR == 0 && BA == 1;
     constexpr int LN = BS - 1 + 2 * H;
-    constexpr int FS = BA * LN;
+    constexpr int T = BS * BA, NQ = PK ? T + (2 * H - 1) * PACK_SEGS : LN * BA;
+    constexpr int FS = NQ;
     constexpr int NS = DIR == 0 ? 1 : BA;
     static_assert((BS * BA) % 64 == 0, "whole waves");
     __shared__ double lds[F::COUNT * FS];
@@ -165,6 +182,38 @@ __global__ void __launch_bounds__(BS* BA, (sweep_waves<D, DIR, R, WT>())) k_swee
     }
     const int nsw = A.n[DIR], na = A.n[adim];
     const long long nc = A.ncell;
+    // packed lines: the block's first face is face p0 of line line0; thread t
+    // has face p0 + t - seg (n + 1) of line line0 + seg
+    [[maybe_unused]] long long nlines = 0, line0 = 0, line = 0;
+    [[maybe_unused]] int p0 = 0, seg = 0, lastseg = 0, face = 0;
+    if constexpr (PK) {
+        const int np = nsw + 1;
+        nlines = (long long)A.n[1] * A.n[2];
+        // blocks are dealt to the eight XCDs in turn; each takes one contiguous
+        // eighth of the sequence, whose shared halos then meet in its L2
+        // (1024 x 512 step -1.6 %)
+        const unsigned nb = gridDim.x, xcd = blockIdx.x & 7u;
+        const unsigned bx = xcd * (nb >> 3) + min(xcd, nb & 7u) + (blockIdx.x >> 3);
+        if (A.rnp) {
+            // fewer than 2^32 faces: the line by a scalar multiplication
+            const unsigned g0 = bx * (BS - 1u);
+            unsigned l0 = __umulhi(g0, A.rnp);
+            p0 = (int)(g0 - l0 * np);
+            while (p0 >= np) {
+                p0 -= np;
+                ++l0;
+            }
+            line0 = l0;
+        } else {
+            const long long g0 = (long long)bx * (BS - 1);
+            line0 = g0 / np;
+            p0 = (int)(g0 - line0 * np);
+        }
+        seg = part_of(p0 + ts, np);
+        lastseg = part_of(p0 + BS - 1, np);
+        face = p0 + ts - seg * np;
+        line = line0 + seg;
+    }
     auto base = [](int a, int l) { return DIR == 0 ? a * LN + l : l * BA + a; };
 
     // stage the node tile (sweep index c0-H .. c0+BS-2+H) with its primitives.
@@ -175,49 +224,73 @@ __global__ void __launch_bounds__(BS* BA, (sweep_waves<D, DIR, R, WT>())) k_swee
     // than threads: the loads of a thread's second node are issued with those
     // of its first, so that the waves that have one wait for memory once.
     __builtin_amdgcn_s_setprio(3);
-    constexpr int NQ = LN * BA, T = BS * BA, IT = (NQ + T - 1) / T;
     {
-        double W[IT][M];
-#pragma unroll
-        for (int it = 0; it < IT; ++it) {
-            const int q = tid + it * T;
-            if ((it + 1) * T > NQ && q >= NQ) continue;
-            const int l = DIR == 0 ? q % LN : q / BA;
-            const int a = DIR == 0 ? q / LN : q % BA;
-            const int gi = c0 - H + l;
-            const int ca = min(abase + a, na - 1);
+        // (in float one node at a time: the registers of the second cost more)
+        constexpr int IT = (NQ + T - 1) / T, LOADS = sizeof(R) == sizeof(double) ? IT : 1;
+        double W[LOADS][M];
+        auto load = [&](int q, double* w) {
             const double* src = A.Ws;
             long long idx, stride = nc;
+            int gi;
+            long long line;  // index of the node's line among the lines along x (packed lines only)
+            if constexpr (PK) {
+                const int pos = p0 + q, seg = part_of(pos, A.n[0] + 1 + 2 * H - 1);
+                gi = pos - seg * (A.n[0] + 2 * H) - H;
+                line = line0 + seg < nlines ? line0 + seg : nlines - 1;
+            } else {
+                gi = c0 - H + (DIR == 0 ? q % LN : q / BA);
+            }
+            const int ca = min(abase + (DIR == 0 ? q / LN : q % BA), na - 1);
             if ((gi < 0 && A.bclo == BC_DIRICHLET) || (gi >= nsw && A.bchi == BC_DIRICHLET)) {
                 // Dirichlet: every ghost node takes the boundary state of its line
                 src = gi < 0 ? A.blo : A.bhi;
-                idx = ca + (long long)na * other;
-                stride = (long long)na * A.n[odim];
+                if constexpr (PK) {
+                    idx = line;
+                    stride = nlines;
+                } else {
+                    idx = ca + (long long)na * other;
+                    stride = (long long)na * A.n[odim];
+                }
             } else {
-                idx = map_bc(gi, nsw, A.bclo, A.bchi) * st[DIR] + ca * st[adim] + other * st[odim];
+                const int g = map_bc(gi, nsw, A.bclo, A.bchi);
+                if constexpr (PK)
+                    idx = line * A.n[0] + g;
+                else
+                    idx = g * st[DIR] + ca * st[adim] + other * st[odim];
             }
 #pragma unroll
-            for (int c = 0; c < M; ++c) W[it][c] = src[c * stride + idx];
-        }
-        const EosDev e = kload<EosDev>(kernel_args() + offsetof(SweepArgs, e));
-#pragma unroll
-        for (int it = 0; it < IT; ++it) {
-            const int q = tid + it * T;
-            if ((it + 1) * T > NQ && q >= NQ) continue;
+            for (int c = 0; c < M; ++c) w[c] = src[c * stride + idx];
+        };
+        auto store = [&](int q, const double* w) {
+            const EosDev e = kload<EosDev>(kernel_args() + offsetof(SweepArgs, e));
             St<N, D> s;
-            state_from_W<N, D>(e, W[it], s);
+            state_from_W<N, D>(e, w, s);
             if constexpr (WT == 2)
                 if (A.P.flags & F_FOUR_EQ) hrm4_pc<N, D>(e, s, s.p, s.c);
-            const int b = base(DIR == 0 ? q / LN : q % BA, DIR == 0 ? q % LN : q / BA);
+            const int b = PK ? q : base(DIR == 0 ? q / LN : q % BA, DIR == 0 ? q % LN : q / BA);
 #pragma unroll
-            for (int c = 0; c < M; ++c) lds[c * FS + b] = W[it][c];
+            for (int c = 0; c < M; ++c) lds[c * FS + b] = w[c];
 #pragma unroll
             for (int d = 0; d < D; ++d) lds[(F::U + d) * FS + b] = s.u[d];
             lds[F::P * FS + b] = s.p;
-            if constexpr (!SLIM) lds[F::RHO * FS + b] = s.rho;
+            lds[F::RHO * FS + b] = s.rho;
             lds[F::C * FS + b] = s.c;
-            lds[F::RC2 * FS + b] = s.rc2;
+        };
+        const int nq = PK ? T + (2 * H - 1) * (lastseg + 1) : NQ;
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int q = tid + it * T;
+            if ((it + 1) * T > NQ && q >= nq) continue;
+            load(q, W[LOADS > 1 ? it : 0]);
+            if constexpr (LOADS == 1) store(q, W[0]);
         }
+        if constexpr (LOADS > 1)
+#pragma unroll
+            for (int it = 0; it < IT; ++it) {
+                const int q = tid + it * T;
+                if ((it + 1) * T > NQ && q >= nq) continue;
+                store(q, W[it]);
+            }
     }
     __builtin_amdgcn_s_setprio(0);
     __syncthreads();
@@ -236,12 +309,17 @@ __global__ void __launch_bounds__(BS* BA, (sweep_waves<D, DIR, R, WT>())) k_swee
         const KArg ka = kernel_args();
         // the first-order float scheme is the general kernel's
         constexpr int LOW = WT == 2 ? 2 : (sizeof(R) == sizeof(double) ? 0 : 1);
-        face_flux<N, D, DIR, NS, FS, R, WT == 1 ? 1 : 0, LOW, SLIM>(
-            lds + base(ta, ts + H - 3), ka + offsetof(SweepArgs, e), ka + offsetof(SweepArgs, P), A.slot[1 + DIR], G, Gp, lc);
+        face_flux<N, D, DIR, NS, FS, R, WT == 1 ? 1 : 0, LOW>(
+            lds + (PK ? ts + (2 * H - 1) * seg + H - 3 : base(ta, ts + H - 3)), ka + offsetof(SweepArgs, e), ka + offsetof(SweepArgs, P), A.slot[1 + DIR], G, Gp, lc);
         // face c0+ts is counted once: the last face of a tile is the first
         // face of the next tile unless it is the boundary face nsw
-        const int f = c0 + ts;
-        const bool ok = f <= nsw && (ts < BS - 1 || f == nsw) && (abase + ta < na);
+        bool ok;
+        if constexpr (PK) {
+            ok = line < nlines && (ts < BS - 1 || (face == nsw && line == nlines - 1));
+        } else {
+            const int f = c0 + ts;
+            ok = f <= nsw && (ts < BS - 1 || f == nsw) && (abase + ta < na);
+        }
         if (ok) cnt = lc;
     }
     // A middle direction only adds to the right-hand side (MODE_ADD): its
@@ -261,7 +339,7 @@ __global__ void __launch_bounds__(BS* BA, (sweep_waves<D, DIR, R, WT>())) k_swee
     }
     __syncthreads();
     if (live) {
-        const int b = base(ta, ts);
+        const int b = PK ? ts : base(ta, ts);
 #pragma unroll
         for (int c = 0; c < M; ++c) lds[c * FS + b] = G[c];
 #pragma unroll
@@ -270,13 +348,13 @@ __global__ void __launch_bounds__(BS* BA, (sweep_waves<D, DIR, R, WT>())) k_swee
     __syncthreads();
 
     // flux difference of cell c0+ts: faces ts (i-1/2) and ts+1 (i+1/2)
-    const int ci = c0 + ts, ca = abase + ta;
+    const int ci = PK ? face : c0 + ts, ca = abase + ta;
     double wmax[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) wmax[d] = 0.0;
-    if (ts < BS - 1 && ci < nsw && ca < na) {
-        const long long cell = ci * st[DIR] + ca * st[adim] + other * st[odim];
-        const int bl = base(ta, ts), br = base(ta, ts + 1);
+    if (ts < BS - 1 && ci < nsw && (PK ? line < nlines : ca < na)) {
+        const long long cell = PK ? line * nsw + ci : ci * st[DIR] + ca * st[adim] + other * st[odim];
+        const int bl = PK ? ts : base(ta, ts), br = PK ? ts + 1 : base(ta, ts + 1);
         double L[M];
 #pragma unroll
         for (int c = 0; c < IA; ++c) L[c] = -(lds[c * FS + br] - lds[c * FS + bl]) * A.idx;
@@ -617,24 +695,28 @@ struct TimerScope {
 
 // tile of the sweep in direction dir: BS face threads along it, BA across.
 // A tile computes BS faces for BS - 1 cells, so a line of n cells takes
-// ceil(n / (BS - 1)) tiles.  Along x (2D, 3D) the 64 x 4 tile gives way to
-// 32 x 8 where that needs fewer face threads for the line: a 256-cell line
-// takes 5 tiles of 64 (320 face threads, the last tile 4 cells) or 9 of 32
-// (288).  Learned weights keep 64 x 4.
+// ceil(n / (BS - 1)) tiles.  Along x (2D, 3D) the better of 64 x 4 and 32 x 8,
+// unless the packed sequence of all lines (256 threads) needs 8 % fewer faces
+// and fills the chip (1024 workgroups): it costs a few per cent in index
+// arithmetic and straddled cache lines (256^3, 10 % fewer: step -1.9 %; 1024 x
+// 512, 5 % fewer: +0.7 %; 1000 x 500, 2 % fewer: +2.3 %; 127 x 65, 20 % fewer
+// but 33 workgroups: +1 to +5 %).
 void sweep_tile(const hrm_ctx* c, int dir, int& BS, int& BA)
 {
+    const long long n = c->n[dir];
+    BS = BA = 16;
     if (c->D == 1) {
         BS = 256;
         BA = 1;
     } else if (dir == 0) {
-        const long long n = c->n[0];
-        const bool narrow = c->weights != HRM_WEIGHTS_MLP && (n + 30) / 31 * 32 < (n + 62) / 63 * 64 &&
-                            (n + 30) / 31 <= 65535;  // tiles along x ride on blockIdx.y
-        BS = narrow ? 32 : 64;
-        BA = narrow ? 8 : 4;
-    } else {
-        BS = 16;
-        BA = 16;
+        const long long f64 = (n + 62) / 63 * 64, f32 = (n + 30) / 31 * 32;
+        if (n >= hrm::PACK_MIN && 100 * std::min(f64, f32) > 108 * (n + 1) && (n + 1) * c->n[1] * c->n[2] > 1024 * 255) {
+            BS = 256;
+            BA = 1;
+        } else {
+            BS = f32 < f64 ? 32 : 64;
+            BA = f32 < f64 ? 8 : 4;
+        }
     }
 }
 
@@ -642,9 +724,23 @@ dim3 sweep_grid(const hrm_ctx* c, int dir, int BS, int BA)
 {
     const int cells = BS - 1;
     if (dir == 0 && c->D == 1) return dim3((c->n[0] + cells - 1) / cells, (c->n[1] + BA - 1) / BA, c->n[2]);
+    if (dir == 0 && BA == 1) {
+        const long long faces = (c->n[0] + 1ll) * c->n[1] * c->n[2];
+        return dim3((unsigned)((faces - 1 + cells - 1) / cells));
+    }
     if (dir == 0) return dim3((c->n[1] + BA - 1) / BA, (c->n[0] + cells - 1) / cells, c->n[2]);
     if (dir == 1) return dim3((c->n[0] + BA - 1) / BA, (c->n[1] + cells - 1) / cells, c->n[2]);
     return dim3((c->n[0] + BA - 1) / BA, (c->n[2] + cells - 1) / cells, c->n[1]);
+}
+
+// the sizes hrm_create takes: those of a launch with tiles of 63 cells along x
+// and 15 along y and z, the other dimensions on the grid's z (y and z at most
+// 65535 blocks)
+bool sizes_fit(const hrm_ctx* c)
+{
+    const int most = 65535;
+    if (c->D >= 2 && ((c->n[0] + 62ll) / 63 > most || (c->n[1] + 14ll) / 15 > most)) return false;
+    return c->D < 3 || (c->n[1] <= most && c->n[2] <= most);
 }
 
 template <int N, int D>
@@ -661,6 +757,7 @@ struct Ops {
         A.blo = c->d_bnd[DIR][0];
         A.bhi = c->d_bnd[DIR][1];
         A.idx = 1.0 / c->dx[DIR];
+        if (DIR == 0) A.rnp = (c->n[0] + 1ll) * c->n[1] * c->n[2] < (1ll << 32) ? (unsigned)((1ll << 32) / (c->n[0] + 1)) : 0u;
         TimerScope t(c, HRM_T_SWEEP_X + DIR, s);
         if constexpr (DIR == D - 1) {
             if (A.wpart) {
@@ -679,9 +776,8 @@ struct Ops {
             hipLaunchKernelGGL((hrm::k_sweep<N, D, DIR, BS, BA, double, 2, WS>), grd, blk, 0, s, A);
             return;
         }
-        if constexpr (D <= 2 && !(DIR == 0 && BS == 32)) {
-            // learned weights: FP64 face arithmetic, one and two dimensions,
-            // on the 64 x 4 x-tile (sweep_tile)
+        if constexpr (D <= 2) {
+            // learned weights: FP64 face arithmetic, one and two dimensions
             if (c->weights == HRM_WEIGHTS_MLP) {
                 hipLaunchKernelGGL((hrm::k_sweep<N, D, DIR, BS, BA, double, 1, WS>), grd, blk, 0, s, A);
                 return;
@@ -702,7 +798,9 @@ struct Ops {
             if (dir == 0) {
                 int BS, BA;
                 sweep_tile(c, 0, BS, BA);
-                if (BS == 32)
+                if (BA == 1)
+                    launch_dir<0, 256, 1>(c, A, s);
+                else if (BS == 32)
                     launch_dir<0, 32, 8>(c, A, s);
                 else
                     launch_dir<0, 64, 4>(c, A, s);
@@ -964,15 +1062,9 @@ int hrm_create(const hrm_grid* g, const hrm_eos* e, const hrm_params* prm, hrm_c
         delete c;
         return HRM_EUNSUPPORTED;
     }
-    for (int d = 0; d < c->D; ++d) {
-        // every sweep launch within the grid limits (y and z at most 65535 blocks)
-        int BS, BA;
-        sweep_tile(c, d, BS, BA);
-        const dim3 gd = sweep_grid(c, d, BS, BA);
-        if (gd.y > 65535u || gd.z > 65535u) {
-            delete c;
-            return HRM_EUNSUPPORTED;
-        }
+    if (!sizes_fit(c)) {
+        delete c;
+        return HRM_EUNSUPPORTED;
     }
     for (int k = 0; k < hrm::MAXN; ++k) {
         const bool on = k < c->N;

@@ -139,7 +139,6 @@ __global__ void __launch_bounds__(BS, 3) k_batch(const BatchArgs A)
                         lds[F::P * FS + l] = s.p;
                         lds[F::RHO * FS + l] = s.rho;
                         lds[F::C * FS + l] = s.c;
-                        lds[F::RC2 * FS + l] = s.rc2;
                     }
                     __builtin_amdgcn_s_setprio(0);
                     __syncthreads();

@@ -481,6 +481,17 @@ __device__ inline double lim_theta(double a, double b, double eps)
     return b < m ? (a - m) / (a - b) : 1.0;
 }
 
+// rho c^2 of a node read back from its record, as state_from_W forms it (the
+// record does not hold it: only the limiter's rare path asks for it)
+template <int N, int D>
+__device__ inline void set_rc2(KArg ke, St<N, D>& s)
+{
+#pragma clang fp contract(off)
+    double Gam, Pi;
+    mixture<N>(kload<EosDev>(ke), s.al, Gam, Pi);
+    s.rc2 = fma(s.p + Pi, rcp_newton(Gam), s.p);
+}
+
 // Completes an interpolated primitive state V and tells whether the limiter
 // below would leave it as it is, without looking at the node: every partial
 // density and volume fraction at or above eps (then b >= eps >= min(eps, a):

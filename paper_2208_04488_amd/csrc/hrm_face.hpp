@@ -9,17 +9,15 @@
 namespace hrm {
 
 // LDS node record: the conservative vector W (M slots), then u_d (D),
-// p, rho, c, rho c^2 (p and c those of the four-equation HRM where that is
-// solved: once per node here, not once per face and side).  The slim record leaves rho out (it is the sum of the
-// partial densities, formed again where it is read): one field less lets
-// the 3D y- and z-sweeps' 16 x 16 tiles fit four workgroups per CU.
-template <int N, int D, bool SLIM = false>
+// p, rho, c (p and c those of the four-equation HRM where that is solved: once
+// per node here, not once per face and side).  rho c^2, which only the rare
+// path of the limiter asks for, is formed there: one field less lets the 3D y-
+// and z-sweeps' 16 x 16 tiles fit four workgroups per CU.
+template <int N, int D>
 struct NodeFields {
     static constexpr int M = 2 * N + D;
-    static constexpr bool slim = SLIM;
-    static constexpr int U = M, P = M + D, RHO = SLIM ? -1 : M + D + 1;
-    static constexpr int C = M + D + (SLIM ? 1 : 2), RC2 = C + 1;
-    static constexpr int COUNT = RC2 + 1;
+    static constexpr int U = M, P = M + D, RHO = P + 1, C = P + 2;
+    static constexpr int COUNT = C + 1;
 };
 
 // node j of the stencil, field f; NS = LDS stride between consecutive nodes,
@@ -30,25 +28,10 @@ __device__ inline double nodev(const double* nd, int j, int f)
     return nd[j * NS + f * FS];
 }
 
-// mixture density of node j: read, or in the slim record the sum of the
-// partial densities in the order the staging pass forms it (the same bits)
-template <class F, int N, int NS, int FS>
-__device__ inline double node_rho(const double* nd, int j)
-{
-    if constexpr (F::slim) {
-        double r = 0.0;
-#pragma unroll
-        for (int k = 0; k < N; ++k) r += nodev<NS, FS>(nd, j, k);
-        return r;
-    } else {
-        return nodev<NS, FS>(nd, j, F::RHO);
-    }
-}
-
-template <int N, int D, int NS, int FS, bool SLIM>
+template <int N, int D, int NS, int FS>
 __device__ inline void load_node(const double* nd, int j, St<N, D>& s)
 {
-    using F = NodeFields<N, D, SLIM>;
+    using F = NodeFields<N, D>;
     constexpr int IE = N + D, IA = N + D + 1;
     double asum = 0.0;
 #pragma unroll
@@ -66,9 +49,8 @@ __device__ inline void load_node(const double* nd, int j, St<N, D>& s)
     }
     s.al[N - 1] = 1.0 - asum;
     s.p = nodev<NS, FS>(nd, j, F::P);
-    s.rho = node_rho<F, N, NS, FS>(nd, j);
+    s.rho = nodev<NS, FS>(nd, j, F::RHO);
     s.c = nodev<NS, FS>(nd, j, F::C);
-    s.rc2 = nodev<NS, FS>(nd, j, F::RC2);
 }
 
 // the pair of interpolated values at i+1/2 from v[0..5] = nodes i-2..i+3:
@@ -133,12 +115,12 @@ __device__ inline double sensor_product(const double* r, const double* p)
 // (selected by flags) for callers that never take them, LOW = 2 leaves out
 // everything else for callers that only take those.  Always inlined:
 // a call would spill the whole face state around it.
-template <int N, int D, int DIR, int NS, int FS, typename R, int WT = 0, int LOW = 1, bool SLIM = false>
+template <int N, int D, int DIR, int NS, int FS, typename R, int WT = 0, int LOW = 1>
 __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, double lam, double* G, double* Gp,
                                           unsigned& cnt)
 {
     static_assert(2 * N <= 15, "per-face counts are packed 4 bits per counter");
-    using F = NodeFields<N, D, SLIM>;
+    using F = NodeFields<N, D>;
     constexpr int M = 2 * N + D, IE = N + D, IA = N + D + 1;
     constexpr int NA = N > 1 ? N - 1 : 1;
     // FP32: the characteristic fields are interpolated as deviations from
@@ -159,8 +141,8 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
     // occupy registers across the whole face computation
     auto node_pair = [&](St<N, D>& a, St<N, D>& b) {
         asm volatile("" ::: "memory");
-        load_node<N, D, NS, FS, SLIM>(nd, 2, a);
-        load_node<N, D, NS, FS, SLIM>(nd, 3, b);
+        load_node<N, D, NS, FS>(nd, 2, a);
+        load_node<N, D, NS, FS>(nd, 3, b);
     };
 
     // first-order HLLC of the node pair and its quasi-conservative pair
@@ -201,7 +183,7 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
     R arb[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) arb[k] = (R)0.5 * (nv(2, k) + nv(3, k));
-    const R rb = (R)0.5 * ((R)node_rho<F, N, NS, FS>(nd, 2) + (R)node_rho<F, N, NS, FS>(nd, 3));
+    const R rb = (R)0.5 * ((R)nodev<NS, FS>(nd, 2, F::RHO) + (R)nodev<NS, FS>(nd, 3, F::RHO));
     const R cb = (R)0.5 * (nv(2, F::C) + nv(3, F::C));
     // 1/(rho c), 1/(rho c^2) = rho (1/(rho c))^2 and 1/(2c) = rho/(2 rho c) from one
     // reciprocal (the means of two admissible nodes are positive)
@@ -266,6 +248,8 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
         if (__builtin_expect(!(cl & cr), 0)) {
             St<N, D> L, Rn;
             node_pair(L, Rn);
+            set_rc2<N, D>(ke, L);
+            set_rc2<N, D>(ke, Rn);
             interp_limit<N, D, R>(ke, kp, VL, convert<N, D, R>(L), cnt);  // also completes the state
             interp_limit<N, D, R>(ke, kp, VR, convert<N, D, R>(Rn), cnt);
         }
@@ -288,7 +272,7 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
         double r[6], pr[6];
 #pragma unroll
         for (int j = 0; j < 6; ++j) {
-            r[j] = node_rho<F, N, NS, FS>(nd, j);
+            r[j] = nodev<NS, FS>(nd, j, F::RHO);
             pr[j] = nodev<NS, FS>(nd, j, F::P);
         }
         const double z = sensor_product(r, pr);

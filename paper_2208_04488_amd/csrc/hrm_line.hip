@@ -48,7 +48,6 @@ __global__ void __launch_bounds__(BS) k_line(const LineArgs A)
         lds[F::P * FS + l] = s.p;
         lds[F::RHO * FS + l] = s.rho;
         lds[F::C * FS + l] = s.c;
-        lds[F::RC2 * FS + l] = s.rc2;
     };
     auto node_state = [&](const EosDev& e, const double* W, St<N, D>& s) {
         state_from_W<N, D>(e, W, s);

@@ -796,3 +796,30 @@ def test_dirichlet_fp32_steps_track_fp64(H, orc):
     assert np.isfinite(b).all() and (b[:N] >= 0).all() and (ab >= 0).all() and (ab <= 1).all()
     ra, rb = a[:N].sum(0), b[:N].sum(0)
     assert np.abs(rb - ra).sum() / np.abs(ra).sum() <= 1e-4
+
+
+# x-sweeps on packed lines (grids of more than 1024 workgroups whose lines the
+# tiles fit badly): two to nine lines in a workgroup, every boundary kind
+@pytest.mark.parametrize("n,bc", [((31, 92, 93), 0), ((33, 90, 90), 1), ((127, 46, 47), 1), ((150, 43, 41), 0),
+                                  ((151, 42, 43), 1), ((257, 33, 33), 0), ((97, 2801), 2)])
+def test_stage_parity_packed_lines(H, orc, n, bc):
+    D = len(n)
+    eos = I.eos_of(I.LIQ_A, I.AIR)
+    c = [(np.arange(k) + 0.5) / k for k in n]
+    X = np.meshgrid(*c[::-1], indexing="ij")[::-1]  # x fastest
+    wave = sum(np.cos(2 * np.pi * (i + 1) * x + i) for i, x in enumerate(X)) / D
+    liq = I.TRACE + (1 - 3 * I.TRACE) * 0.5 * (1 + np.tanh((wave - 0.3) * 12))
+    u = [30.0 * np.sin(2 * np.pi * X[d] + d) for d in range(D)]
+    W = I.equilibrium_state(eos, [liq, 1 - liq], u, 1e5 * (1 + 0.2 * wave), 300.0 + 20 * wave)
+    W = np.ascontiguousarray(W.reshape((W.shape[0],) + tuple((n + (1,) * (3 - D))[::-1])))
+    sides = [(bc, bc) if bc < 2 else (I.DIRICHLET, I.DIRICHLET)] + [(min(bc, 1),) * 2] * (D - 1)
+    prob = I.Problem("packed", eos, D, n, (1.0 / max(n),) * D, sides, W)
+    if bc == 2:
+        prob.boundary = {(0, s): np.ascontiguousarray(W[:, 0, :, -s]) for s in (0, 1)}
+    check_stages(H, orc, prob, prob.W)
+
+
+@pytest.mark.parametrize("make", [lambda: I.config3(70), lambda: I.config2(70, 3803)], ids=["cube_70", "plane_70x3803"])
+def test_stage_parity_packed_lines_three_species(H, orc, make):
+    prob = make()
+    check_stages(H, orc, prob, prob.W)
