@@ -53,6 +53,12 @@ struct SweepArgs {
     int hold;  // mode 2 within a full RK3 step: a step of dt = 0 (the end time reached) leaves W^n as it is
     double a, b;
     double idx;
+    // lines (D = 1), a step's first two sweeps (phase 1, 2; 0 elsewhere)
+    int phase, npart;
+    double* part;   // wavespeed partials of W^n (npart, the first nslot cleared for the step's last sweep)
+    double* tnext;  // the time after the step, from phase 1 to phase 2
+    double* slotw;  // `slot`, to write
+    DtArgs dt;
     EosDev e;
     ParDev P;
 };
@@ -293,7 +299,48 @@ __global__ void __launch_bounds__(BS* BA, (sweep_waves<D, DIR, R, WT>())) k_swee
             }
     }
     __builtin_amdgcn_s_setprio(0);
-    __syncthreads();
+    // On a line every sweep spans all of it, so the step's first sweep takes
+    // the maximum of the wavespeed partials itself, every workgroup the same
+    // one, and forms the time step that it works with; its first workgroup
+    // leaves it for the later sweeps.  The second sweep's first workgroup, when
+    // nobody reads them any more, advances the device time and clears the
+    // partials for the third to fold into.  That saves the launch of
+    // k_reduce_dt, a fifth of a short first-order step.
+    double dt_step = 0.0, lam = 0.0;
+    if constexpr (D == 1) {
+        __shared__ double shm[T / 64];
+        if (A.phase == 1) {
+            double m = 0.0;
+            for (int i = tid; i < A.npart; i += T) m = nmax(m, A.part[i]);
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) m = nmax(m, __shfl_xor(m, off, 64));
+            if ((tid & 63) == 0) shm[tid >> 6] = m;
+        }
+        __syncthreads();
+        if (A.phase == 1) {
+            double m = shm[0], slot[5] = {0.0, 0.0, 0.0, 0.0, A.slot[4]};
+#pragma unroll
+            for (int i = 1; i < T / 64; ++i) m = nmax(m, shm[i]);
+            dt_from_max(&m, A.dt, slot);
+            dt_step = slot[0];
+            lam = slot[1];
+            if (tid == 0 && blockIdx.x == 0) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) A.slotw[i] = slot[i];
+                *A.tnext = slot[4];
+            }
+        } else {
+            dt_step = A.slot[0];
+            lam = A.slot[1];
+            if (A.phase == 2 && blockIdx.x == 0) {
+                for (int i = tid; i < (int)A.nslot; i += T) A.part[i] = 0.0;
+                if (tid == 0) A.slotw[4] = *A.tnext;
+            }
+        }
+    } else {
+        __syncthreads();
+        lam = A.slot[1 + DIR];
+    }
 
     // one face per thread: between sweep nodes c0-1+ts and c0+ts.  In the
     // z-sweep a wave holds four consecutive ts; one whose faces all lie
@@ -310,7 +357,7 @@ __global__ void __launch_bounds__(BS* BA, (sweep_waves<D, DIR, R, WT>())) k_swee
         // the first-order float scheme is the general kernel's
         constexpr int LOW = WT == 2 ? 2 : (sizeof(R) == sizeof(double) ? 0 : 1);
         face_flux<N, D, DIR, NS, FS, R, WT == 1 ? 1 : 0, LOW>(
-            lds + (PK ? ts + (2 * H - 1) * seg + H - 3 : base(ta, ts + H - 3)), ka + offsetof(SweepArgs, e), ka + offsetof(SweepArgs, P), A.slot[1 + DIR], G, Gp, lc);
+            lds + (PK ? ts + (2 * H - 1) * seg + H - 3 : base(ta, ts + H - 3)), ka + offsetof(SweepArgs, e), ka + offsetof(SweepArgs, P), lam, G, Gp, lc);
         // face c0+ts is counted once: the last face of a tile is the first
         // face of the next tile unless it is the boundary face nsw
         bool ok;
@@ -372,7 +419,7 @@ __global__ void __launch_bounds__(BS* BA, (sweep_waves<D, DIR, R, WT>())) k_swee
                 for (int c = 0; c < M; ++c) A.rhs[c * nc + cell] += L[c];
             }
         } else {
-            const double dt = A.slot[0];
+            const double dt = D == 1 ? dt_step : A.slot[0];
             double w[M];
             if (__builtin_expect(A.hold && dt == 0.0, 0)) {
                 // every stage of a step of length 0 is W^n in exact arithmetic;
@@ -902,7 +949,8 @@ int check_boundary(hrm_ctx* c);
 // all directions of L(W_s); with `stage` the last one applies the stage
 // update (and writes the wavespeed partials of its output into wpart)
 int run_operator(hrm_ctx* c, const double* Ws, const double* Wn, double* Wout, double* rhs, const double* slot,
-                 bool stage, double a, double b, int relax, hipStream_t s, double* wpart = nullptr, int hold = 0)
+                 bool stage, double a, double b, int relax, hipStream_t s, double* wpart = nullptr, int hold = 0,
+                 int phase = 0, const hrm::DtArgs* dt = nullptr)
 {
     if (c->weights == HRM_WEIGHTS_MLP && !c->mlp_ready)
         return fail(c, HRM_EINVAL, "learned weights selected but hrm_set_mlp not called%s");
@@ -919,6 +967,16 @@ int run_operator(hrm_ctx* c, const double* Ws, const double* Wn, double* Wout, d
     A.hold = hold;
     A.wpart = stage ? wpart : nullptr;
     A.nslot = (unsigned)c->nslot;
+    if (phase) {
+        A.phase = phase;
+        A.part = c->d_part;
+        A.npart = c->nslot;
+        for (int side = 0; side < 2; ++side)
+            if (c->d_bnd[0][side]) A.npart += c->nbpart[0];
+        A.tnext = c->d_maxs;
+        A.slotw = const_cast<double*>(slot);
+        A.dt = *dt;
+    }
     int rc = HRM_OK;
     for (int d = 0; d < c->D; ++d) {
         const bool last = d == c->D - 1;
@@ -973,12 +1031,15 @@ int step_enqueue(hrm_ctx* c, double* d_W, double cfl, double dt_fixed, double t_
     static const double RK_B[3] = {1.0, 1.0 / 4.0, 2.0 / 3.0};
     const hrm::DtArgs a = dt_args(c, cfl, dt_fixed, t_end);
     int rc = check_boundary(c);
-    if (rc == HRM_OK) rc = dispatch(c, [&](auto ops) { decltype(ops)::reduce_dt(c, a, d_slot, s); });
+    const bool line = c->D == 1;  // the first sweep takes the time step itself
+    if (rc == HRM_OK && !line) rc = dispatch(c, [&](auto ops) { decltype(ops)::reduce_dt(c, a, d_slot, s); });
     if (rc == HRM_OK) rc = check_launch(c, "hrm_advance time step");
     if (rc == HRM_OK)
-        rc = run_operator(c, d_W, d_W, c->d_W1, c->d_rhs, d_slot, true, RK_A[0], RK_B[0], 1, s, nullptr, 1);
+        rc = run_operator(c, d_W, d_W, c->d_W1, c->d_rhs, d_slot, true, RK_A[0], RK_B[0], 1, s, nullptr, 1,
+                          line ? 1 : 0, &a);
     if (rc == HRM_OK)
-        rc = run_operator(c, c->d_W1, d_W, c->d_W2, c->d_rhs, d_slot, true, RK_A[1], RK_B[1], 1, s, nullptr, 1);
+        rc = run_operator(c, c->d_W1, d_W, c->d_W2, c->d_rhs, d_slot, true, RK_A[1], RK_B[1], 1, s, nullptr, 1,
+                          line ? 2 : 0, &a);
     if (rc == HRM_OK)
         rc = run_operator(c, c->d_W2, d_W, d_W, c->d_rhs, d_slot, true, RK_A[2], RK_B[2], 1, s, c->d_part, 1);
     return rc;

@@ -941,19 +941,8 @@ __device__ inline bool relax_cell(const EosDev& e, double* W)
 // a quotient of positive terms (no cancellation, unlike 2 A_p p + B_p).
 // p = c = NaN outside the admissible set.
 template <int N, int D>
-__device__ inline void hrm4_pc(const EosDev& e, const St<N, D>& s, double& p, double& c)
+__device__ inline double hrm4_c(const EosDev& e, const St<N, D>& s, double p)
 {
-    double w[N + D + 1];
-#pragma unroll
-    for (int k = 0; k < N; ++k) w[k] = s.ar[k];
-#pragma unroll
-    for (int d = 0; d < D; ++d) w[N + d] = s.mom[d];
-    w[N + D] = s.E;
-    double T;
-    if (!relaxed_pT<N, D>(e, w, p, T)) {
-        p = c = __builtin_nan("");
-        return;
-    }
     double rho = 0.0, Sv = 0.0, SR = 0.0, rq = 0.0, m2 = 0.0;
 #pragma unroll
     for (int k = 0; k < N; ++k) {
@@ -967,7 +956,22 @@ __device__ inline void hrm4_pc(const EosDev& e, const St<N, D>& s, double& p, do
     const double re = s.E - div_rn(0.5 * m2, rho) - rq;
     const double S2 = SR - s.ar[0] * (e.cp[0] - e.cv[0]);
     const double p1 = e.pinf[0];
-    c = sqrt_rn(div_rn(p * (re + p) * (SR * p + p1 * S2), rho * (Sv * p * p + re * p1 * S2)));
+    return sqrt_rn(div_rn(p * (re + p) * (SR * p + p1 * S2), rho * (Sv * p * p + re * p1 * S2)));
+}
+
+template <int N, int D>
+__device__ inline void hrm4_pc(const EosDev& e, const St<N, D>& s, double& p, double& c)
+{
+    double w[N + D + 1], T;
+#pragma unroll
+    for (int k = 0; k < N; ++k) w[k] = s.ar[k];
+#pragma unroll
+    for (int d = 0; d < D; ++d) w[N + d] = s.mom[d];
+    w[N + D] = s.E;
+    if (relaxed_pT<N, D>(e, w, p, T))
+        c = hrm4_c<N, D>(e, s, p);
+    else
+        p = c = __builtin_nan("");
 }
 
 struct DtArgs {

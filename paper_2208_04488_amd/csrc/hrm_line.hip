@@ -112,7 +112,9 @@ __global__ void __launch_bounds__(BS) k_line(const LineArgs A)
             if (live) {
                 unsigned lc = 0;
                 const KArg ka = kernel_args();
-                face_flux<N, D, 0, 1, FS, R, 0, LOW>(lds + ts, ka + offsetof(LineArgs, e), ka + offsetof(LineArgs, P), slot[1],
+                // lanes beyond face n repeat it: whatever LDS holds there would
+                // send the whole wave through the limiters' rare paths
+                face_flux<N, D, 0, 1, FS, R, 0, LOW>(lds + min(ts, n), ka + offsetof(LineArgs, e), ka + offsetof(LineArgs, P), slot[1],
                                              G, Gp, lc);
                 if (ts <= n) cnt = lc;
             }
