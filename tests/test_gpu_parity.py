@@ -823,3 +823,41 @@ def test_stage_parity_packed_lines(H, orc, n, bc):
 def test_stage_parity_packed_lines_three_species(H, orc, make):
     prob = make()
     check_stages(H, orc, prob, prob.W)
+
+
+@pytest.mark.parametrize("n,offset", [((6,), 0), ((7,), 0), ((6,), 1), ((130, 4), 0), ((129, 3), 0), ((130, 4), 1)])
+def test_pointwise_kernels_two_cells_per_thread(H, n, offset):
+    """Even cell counts at 16-byte addresses take two cells per thread, odd ones
+    and 8-byte addresses one: the same bits either way, and cells the relaxation
+    rejects stay as they are."""
+    import torch
+    D, cells = len(n), int(np.prod(n))
+    eos = I.eos_of(I.LIQ_B, I.AIR, I.HELIUM)
+    W = I.random_admissible(eos, D, cells, seed=5)
+    W[3 + D, 1::4] = -1.0  # negative energy: no relaxed state
+    nn = n + (1,) * (3 - D)
+    prob = I.Problem("pointwise", eos, D, n, (1e-3,) * D, [(0, 0)] * D,
+                     np.ascontiguousarray(W.reshape((W.shape[0],) + nn[::-1])))
+    s = H.Solver(prob)
+
+    def at(off, like):
+        buf = torch.zeros(like.numel() + 2, dtype=torch.float64, device="cuda")
+        return buf[off:off + like.numel()].view(like.shape).copy_(like)
+
+    outs = []
+    for off in (1, offset):  # one cell per thread, then the case
+        Wd = at(off, s.W)
+        eq = [at(off, torch.zeros(cells, dtype=torch.float64, device="cuda")) for _ in range(3)]
+        H.hrm_equilibrium_state(s.ctx, Wd, *eq)
+        ok = torch.isfinite(eq[0])
+        H.hrm_relax(s.ctx, Wd)
+        good = at(off, torch.where(ok, s.W.reshape(s.W.shape[0], -1), s.W.reshape(s.W.shape[0], -1)[:, :1]))
+        H.hrm_max_wavespeed(s.ctx, good, s.maxs)
+        torch.cuda.synchronize()
+        outs.append([t.clone() for t in (Wd, *eq, s.maxs)])
+    assert s.diagnostics()["relax_bad"] == 2 * len(range(1, cells, 4))
+    for a, b in zip(*outs):
+        assert torch.equal(torch.nan_to_num(a, nan=-7.0), torch.nan_to_num(b, nan=-7.0))
+    bad = torch.arange(cells, device="cuda") % 4 == 1
+    assert torch.equal(outs[1][0].reshape(s.W.shape[0], -1)[:, bad], s.W.reshape(s.W.shape[0], -1)[:, bad])
+    s.close()
