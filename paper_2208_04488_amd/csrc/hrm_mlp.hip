@@ -10,6 +10,7 @@
 // interpolant on the vector ALUs.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -649,12 +650,8 @@ int hrm_mlp_adam(float* d_params, const float* d_grad, float* d_m, float* d_v, i
     if (!(lr > 0.0f) || !(beta1 >= 0.0f && beta1 < 1.0f) || !(beta2 >= 0.0f && beta2 < 1.0f) || !(eps > 0.0f))
         return HRM_EINVAL;
     // bias corrections 1 - beta^step, formed in double
-    double p1 = 1.0, p2 = 1.0;
-    for (int i = 0; i < step && i < 100000; ++i) {
-        p1 *= beta1;
-        p2 *= beta2;
-    }
-    const float c1 = (float)(1.0 - p1), c2 = (float)(1.0 - p2);
+    const int n = step < 100000 ? step : 100000;
+    const float c1 = (float)(1.0 - std::pow((double)beta1, n)), c2 = (float)(1.0 - std::pow((double)beta2, n));
     hipLaunchKernelGGL(hrm::k_mlp_adam, dim3((hrm::MLP_NPARAM + 255) / 256), dim3(256), 0, (hipStream_t)stream,
                        d_params, d_grad, d_m, d_v, lr, beta1, beta2, eps, c1, c2);
     return hipGetLastError() == hipSuccess ? HRM_OK : HRM_EDEVICE;

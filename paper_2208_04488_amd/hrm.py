@@ -116,6 +116,11 @@ def _load():
 
 lib = _load()
 
+import torch  # noqa: E402  (_load imports it before the library)
+
+_f64, _f32 = torch.float64, torch.float32
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
 
 def header_functions(path: str = HEADER):
     """Names of the functions include/hrm.h declares."""
@@ -135,23 +140,25 @@ def _ptr(t) -> int:
         return 0
     if isinstance(t, int):
         return t
-    import torch
-    if not (t.is_cuda and t.dtype == torch.float64 and t.is_contiguous()):
+    if not (t.is_cuda and t.dtype is _f64 and t.is_contiguous()):
         raise ValueError("device arrays must be contiguous float64 CUDA tensors")
     return t.data_ptr()
 
 
 def _ptrf(t) -> int:
     """Device pointer of a contiguous float32 CUDA tensor."""
-    import torch
-    if not (t.is_cuda and t.dtype == torch.float32 and t.is_contiguous()):
+    if not (t.is_cuda and t.dtype is _f32 and t.is_contiguous()):
         raise ValueError("device arrays must be contiguous float32 CUDA tensors")
     return t.data_ptr()
 
 
 def _stream(stream) -> int:
+    """The raw stream: torch's current one by default, asked for without
+    building a Stream object (a call's arguments take longer on the host than
+    the launch of a small kernel)."""
     if stream is None:
-        import torch
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
