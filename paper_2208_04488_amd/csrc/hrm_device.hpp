@@ -329,18 +329,19 @@ __device__ inline void weno_is_pair(const double* v, double eps, double& l, doub
 }
 
 // FP32 variant: the candidates and smoothness indicators are float and only
-// the weighting is done in double, scaled as above.
+// the weighting is done in double, normalised by one reciprocal.
 __device__ inline float weno_is_weigh(float s0, float s1, float s2, float s3, float q0, float q1, float q01, float q2,
                                       float q3, float qt, double eps)
 {
     const double B0 = (double)q0 + eps, B1 = (double)q1 + eps, B01 = (double)q01 + eps;
     const double B2 = (double)q2 + eps, B3 = (double)q3 + eps, tau = qt;
-    const double t2 = tau * tau, B23 = B2 * B3, P = (B0 * B1) * B01;
-    const double E0 = fma(B0, B01, t2) * (B1 * B23), E1 = fma(B1, B01, t2) * (B0 * B23);
-    const double E2 = fma(tau, B3, B23) * P, E3 = fma(tau, B2, B23) * P;
-    const double inv = rcp_newton(fma(3.0, E0, fma(2.0, E2, fma(0.4, E3, E1))));
-    return (float)(3.0 * (E0 * inv)) * s0 + (float)(E1 * inv) * s1 + (float)(2.0 * (E2 * inv)) * s2 +
-           (float)(0.4 * (E3 * inv)) * s3;
+    const double t2 = tau * tau, B23 = B2 * B3, B0B1 = B0 * B1;
+    const double e0 = (15.0 / 32.0) * (B0 * B01 + t2) * B1 * B23;
+    const double e1 = (5.0 / 32.0) * (B1 * B01 + t2) * B0 * B23;
+    const double e2 = (5.0 / 16.0) * (B2 + tau) * B0B1 * B01 * B3;
+    const double e3 = (1.0 / 16.0) * (B3 + tau) * B0B1 * B01 * B2;
+    const double inv = rcp_newton(e0 + e1 + e2 + e3);
+    return (float)(e0 * inv) * s0 + (float)(e1 * inv) * s1 + (float)(e2 * inv) * s2 + (float)(e3 * inv) * s3;
 }
 
 // the FP32 pair shares the candidate (u_i + u_{i+1})/2, beta_0 and the squared
