@@ -65,13 +65,14 @@ __device__ inline void interp_pair(const R* v, double eps, const MlpPacked* mlp,
     } else {
         const R ul[5] = {v[0], v[1], v[2], v[3], v[4]};
         const R ur[5] = {v[5], v[4], v[3], v[2], v[1]};
+        double dl[5], dr[5];
         float xl[5], xr[5], zl[3], zr[3], wl[3], wr[3];
-        mlp_inputs<R>(ul, xl);
-        mlp_inputs<R>(ur, xr);
+        mlp_inputs(ul, dl, xl);
+        mlp_inputs(ur, dr, xr);
         mlp_logits(mlp, xl, zl);
         mlp_logits(mlp, xr, zr);
-        l = mlp_omega(zl, xl, wl) ? mlp_value<R>(ul, wl) : weno_is(v[0], v[1], v[2], v[3], v[4], eps);
-        r = mlp_omega(zr, xr, wr) ? mlp_value<R>(ur, wr) : weno_is(v[5], v[4], v[3], v[2], v[1], eps);
+        l = mlp_omega(zl, xl, wl) ? mlp_value(v[2], dl, wl) : weno_is(v[0], v[1], v[2], v[3], v[4], eps);
+        r = mlp_omega(zr, xr, wr) ? mlp_value(v[3], dr, wr) : weno_is(v[5], v[4], v[3], v[2], v[1], eps);
     }
 }
 

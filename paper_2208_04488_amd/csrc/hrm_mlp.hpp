@@ -171,28 +171,40 @@ __device__ inline bool mlp_omega(const float* z, const float* x, float* w)
     return isfinite(w[0]) && isfinite(w[1]) && isfinite(w[2]);
 }
 
-// normalised float inputs of a stencil u[0..4] (u[2] the node i)
-template <typename R>
-__device__ inline void mlp_inputs(const R* u, float* x)
+// differences d[j] = u[j] - u[2] of a stencil from its node i (d[2] = 0) and
+// its normalised float inputs; the reciprocal of the spread by Newton's
+// iteration (as rcp_newton) where it is well inside the normal numbers (with
+// the differences kept for mlp_value: 1024 x 512, two steps 846 -> 837 us)
+__device__ inline void mlp_inputs(const double* u, double* d, float* x)
 {
-    R s = (R)0;
+    double s = 0.0;
 #pragma unroll
-    for (int j = 0; j < 5; ++j) s = fmax(s, fabs(u[j] - u[2]));
-    const R r = s > (R)0 ? (R)1 / s : (R)0;
+    for (int j = 0; j < 5; ++j) {
+        d[j] = u[j] - u[2];
+        if (j != 2) s = fmax(s, fabs(d[j]));
+    }
+    double r;
+    if (__builtin_expect(s > 1e-290 && s < 1e290, 1)) {
+        r = __builtin_amdgcn_rcp(s);
+        r = fma(fma(-s, r, 1.0), r, r);
+        r = fma(fma(-s, r, 1.0), r, r);
+    } else {
+        r = s > 0.0 ? 1.0 / s : 0.0;
+    }
 #pragma unroll
-    for (int j = 0; j < 5; ++j) x[j] = (float)((u[j] - u[2]) * r);
+    for (int j = 0; j < 5; ++j) x[j] = j == 2 ? 0.0f : (float)(d[j] * r);
 }
 
 // sum_k w_k S_k written as S_c + w_l (S_l - S_c) + w_r (S_r - S_c): the
 // weights sum to one only to float round-off, and this form keeps a constant
-// stencil exact
-template <typename R>
-__device__ inline R mlp_value(const R* u, const float* w)
+// stencil exact.  The candidates in differences from node i: 8 (S_c - u_i) =
+// 3 d_3 - d_1, 8 (S_l - S_c) = 3 (d_0 - d_3) - 9 d_1, 8 (S_r - S_c) = 3 d_3 + d_1 - d_4.
+__device__ inline double mlp_value(double ui, const double* d, const float* w)
 {
-    const R sl = ((R)3 * u[0] - (R)10 * u[1] + (R)15 * u[2]) / (R)8;
-    const R sc = (-u[1] + (R)6 * u[2] + (R)3 * u[3]) / (R)8;
-    const R sr = ((R)3 * u[2] + (R)6 * u[3] - u[4]) / (R)8;
-    return sc + (R)w[0] * (sl - sc) + (R)w[2] * (sr - sc);
+    const double c = fma(3.0, d[3], -d[1]);
+    const double l = fma(-9.0, d[1], 3.0 * (d[0] - d[3]));
+    const double r = fma(3.0, d[3], d[1]) - d[4];
+    return fma(0.125, fma((double)w[0], l, fma((double)w[2], r, c)), ui);
 }
 
 // ---------------------------------------------------------------- host side

@@ -476,3 +476,22 @@ def test_learned_gain_on_config5_full_size(H, trained):
     print(f"config5 (2048 x 1024) L1(rho) vs exact: plain {r['plain']:.6e}, prior {r['prior']:.6e}, "
           f"trained {r['trained']:.6e} (trained vs prior {r['trained'] / r['prior'] - 1:+.2%}, "
           f"vs plain {r['trained'] / r['plain'] - 1:+.2%})")
+
+
+@pytest.mark.parametrize("power", [-1000, -964, -960, 960, 964, 1000])
+def test_spread_beyond_the_fast_reciprocal(H, M, power):
+    """Stencils scaled by 2^power: the values scale with them whichever way the
+    spread's reciprocal is taken (it leaves the fast way near 2^-963 and 2^963).
+    The inputs may differ by one float rounding, which moves a weight by up to
+    1e-6 (the bound on float weights above), and each weight multiplies a
+    difference of candidates of at most 15/8 spreads."""
+    rng = np.random.default_rng(13)
+    U = rng.normal(size=(500, 5))
+    U[::5] = np.sign(U[::5])
+    U[1::7, 1:] = U[1::7, :1]  # constant but for rounding: no spread
+    p = rand_params(M, 3, 0.3)
+    val, om = infer(H, p, U)
+    vs, os = infer(H, p, np.ldexp(U, power))
+    spread = np.abs(U - U[:, 2:3]).max(axis=1)
+    assert np.abs(om - os).max() <= 1e-6
+    assert (np.abs(np.ldexp(vs, -power) - val) <= 2 * 15 / 8 * 1e-6 * spread + 1e-15 * np.abs(U).max(axis=1)).all()
