@@ -32,19 +32,20 @@ struct BatchArgs {
     const int* order;      // processing order (longest first)
     double* t;             // per-problem time
     const double* tend;    // per-problem end time (<= 0: none)
-    int* queue;
+    int* queue;  // problems taken: in all, from the front, from the back of order
     unsigned long long* cnt;
     long long T;
     int nprob;
     int ksteps;
+    int narrow;  // BS 512: workgroups that keep 256 threads
     double cfl;
     EosDev e;
     ParDev P;
 };
 
-__global__ void k_set_int(int* p, int v)
+__global__ void k_reset_queue(int* p)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *p = v;
+    if (threadIdx.x < 3 && blockIdx.x == 0) p[threadIdx.x] = 0;
 }
 
 // a workgroup-uniform double (read from LDS) moved to scalar registers
@@ -56,6 +57,14 @@ __device__ inline double uniform(double v)
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+// Bound by FP64 issue where problems are plenty (4096 of 200-2000 cells: 640 us a
+// step, three workgroups of 256 threads per CU), else by the chain of tiles of the
+// longest problem.  With few problems a tile of 256 threads leaves a SIMD one wave,
+// whose stalls nothing fills: BS 512 gives a long problem two waves per SIMD and
+// half the tiles, and its first `narrow` workgroups drop to 256 threads (the upper
+// waves end at once and free their registers), so that one of each fits a CU.
+// us a step, 256 threads -> this: 300 of 40-400 cells 40 -> 34, in float 54 -> 38;
+// 500 of 100-800, three species 139 -> 82; 512 of 1000-2000 178 -> 135.
 template <int N, int BS, typename R>
 __global__ void __launch_bounds__(BS, 3) k_batch(const BatchArgs A)
 {
@@ -65,17 +74,29 @@ __global__ void __launch_bounds__(BS, 3) k_batch(const BatchArgs A)
     constexpr int NA = N > 1 ? N - 1 : 1;
     constexpr int LN = BS + 5;
     constexpr int FS = LN;
-    static_assert(BS % 64 == 0 && BS <= 256, "block size");
+    static_assert(BS % 64 == 0 && BS <= 512, "block size");
     __shared__ double lds[F::COUNT * FS];
     __shared__ double sh[12];
     __shared__ double sdt[3];
     __shared__ int spid;
     const int ts = threadIdx.x;
     const long long T = A.T;
-    unsigned cnt[C_N] = {0, 0, 0, 0, 0, 0, 0};
+    const bool narrow = BS == 512 && (int)blockIdx.x < A.narrow;
+    const int bs = narrow ? 256 : BS;
+    if (ts >= bs) return;  // whole waves; the barriers count those that are left
 
     for (;;) {
-        if (ts == 0) spid = atomicAdd(A.queue, 1);
+        if (ts == 0) {
+            if constexpr (BS == 512) {
+                // the wide workgroups take the longest problems and the narrow ones
+                // the shortest; no more than nprob are taken, so the two ends never cross
+                int q = atomicAdd(A.queue, 1);
+                if (q < A.nprob) q = narrow ? A.nprob - 1 - atomicAdd(A.queue + 2, 1) : atomicAdd(A.queue + 1, 1);
+                spid = q;
+            } else {
+                spid = atomicAdd(A.queue, 1);
+            }
+        }
         __syncthreads();
         const int pid = __builtin_amdgcn_readfirstlane(spid);
         __syncthreads();
@@ -89,15 +110,16 @@ __global__ void __launch_bounds__(BS, 3) k_batch(const BatchArgs A)
         for (int step = 0; step < A.ksteps; ++step) {
             // per-problem wavespeed and time step (1D: sigma = 1, lambda = dt/dx)
             double m[1] = {0.0};
-            for (int i = ts; i < n; i += BS) {
+            const EosDev e = kload<EosDev>(kernel_args() + offsetof(BatchArgs, e));
+            for (int i = ts; i < n; i += bs) {
                 double w[M];
 #pragma unroll
                 for (int c = 0; c < M; ++c) w[c] = A.W[c * T + base + i];
                 St<N, D> s;
-                state_from_W<N, D>(A.e, w, s);
+                state_from_W<N, D>(e, w, s);
                 m[0] = nmax(m[0], fabs(s.u[0]) + s.c);
             }
-            block_max<1>(m, sh);
+            block_max<1>(m, sh, bs);
             if (ts == 0) {
                 // the step is clipped so that t does not pass the problem's
                 // end time (as hrm_compute_dt does); a problem that has
@@ -121,12 +143,14 @@ __global__ void __launch_bounds__(BS, 3) k_batch(const BatchArgs A)
                 // Shu-Osher coefficients (a, b) of the three stages
                 const double ca = stage == 0 ? 0.0 : (stage == 1 ? 3.0 / 4.0 : 1.0 / 3.0);
                 const double cb = stage == 0 ? 1.0 : (stage == 1 ? 1.0 / 4.0 : 2.0 / 3.0);
-                for (int c0 = 0; c0 < n; c0 += BS - 1) {
-                    const EosDev& e = A.e;
+                for (int c0 = 0; c0 < n; c0 += bs - 1) {
+                    const KArg ka = kernel_args();
+                    unsigned cnt = 0;  // packed counts (cnt_one)
                     // stage the tile c0-3 .. c0+BS+1 with its primitives
                     // (at raised priority, as in k_sweep)
                     __builtin_amdgcn_s_setprio(3);
-                    for (int l = ts; l < LN; l += BS) {
+                    const EosDev e = kload<EosDev>(ka + offsetof(BatchArgs, e));
+                    for (int l = ts; l < bs + 5 && l <= n + 5 - c0; l += bs) {
                         const int g = map_bc(c0 - 3 + l, n, HRM_BC_TRANSMISSIVE, HRM_BC_TRANSMISSIVE);
                         double W[M];
 #pragma unroll
@@ -149,13 +173,10 @@ __global__ void __launch_bounds__(BS, 3) k_batch(const BatchArgs A)
                     const bool live = c0 + (ts & ~63) <= n;
                     if (live) {
                         unsigned lc = 0;  // packed counts of this face (cnt_one)
-                        const KArg ka = kernel_args();
-                        face_flux<N, D, 0, 1, FS, R, 0, 0>(lds + ts, ka + offsetof(BatchArgs, e),
+                        face_flux<N, D, 0, 1, FS, R, 0, 0>(lds + min(ts, n - c0), ka + offsetof(BatchArgs, e),
                                                                ka + offsetof(BatchArgs, P), lam, G, Gp, lc);
                         const int f = c0 + ts;  // counted once, as in k_sweep
-                        if (f <= n && (ts < BS - 1 || f == n))
-#pragma unroll
-                            for (int k = 0; k < C_N; ++k) cnt[k] += cnt_get(lc, k);
+                        if (f <= n && (ts < bs - 1 || f == n)) cnt = lc;
                     }
                     __syncthreads();
                     if (live) {
@@ -166,7 +187,7 @@ __global__ void __launch_bounds__(BS, 3) k_batch(const BatchArgs A)
                     }
                     __syncthreads();
                     const int ci = c0 + ts;
-                    if (ts < BS - 1 && ci < n) {
+                    if (ts < bs - 1 && ci < n) {
                         const long long cell = base + ci;
                         double w[M];
 #pragma unroll
@@ -175,16 +196,16 @@ __global__ void __launch_bounds__(BS, 3) k_batch(const BatchArgs A)
                             const double L = -(lds[c * FS + ts + 1] - gp) * idx;
                             w[c] = ca * A.W[c * T + cell] + cb * (Ws[c * T + cell] + dt * L);
                         }
-                        if (!relax_cell<N, D>(e, w)) cnt[C_RELAX_BAD]++;
+                        if (!relax_cell<N, D>(kload<EosDev>(ka + offsetof(BatchArgs, e)), w)) cnt += cnt_one(C_RELAX_BAD);
 #pragma unroll
                         for (int c = 0; c < M; ++c) Wout[c * T + cell] = w[c];
                     }
+                    flush_counters(cnt, A.cnt);
                     __syncthreads();
                 }
             }
         }
     }
-    flush_counters(cnt, A.cnt);
 }
 
 }  // namespace hrm
@@ -203,7 +224,7 @@ struct hrm_batch {
     double* d_tend;
     int* d_queue;
     unsigned long long* d_cnt;
-    int threads, blocks, ksteps;
+    int threads, blocks, narrow, ksteps;
     hipStream_t cap_stream;
     hipGraphExec_t gexec;
     double* g_W;
@@ -236,6 +257,7 @@ int launch_n(hrm_batch* b, const hrm::BatchArgs& A, hipStream_t s)
     case 64: launch_bs<N, 64>(b, A, s); return HRM_OK;
     case 128: launch_bs<N, 128>(b, A, s); return HRM_OK;
     case 256: launch_bs<N, 256>(b, A, s); return HRM_OK;
+    case 512: launch_bs<N, 512>(b, A, s); return HRM_OK;
     default: return bfail(b, HRM_EINVAL, "hrm_batch: threads must be 64, 128 or 256");
     }
 }
@@ -258,10 +280,11 @@ int enqueue_chunk(hrm_batch* b, double* d_W, double cfl, hipStream_t s)
     A.T = b->T;
     A.nprob = b->nprob;
     A.ksteps = b->ksteps;
+    A.narrow = b->narrow;
     A.cfl = cfl;
     A.e = b->eos;
     A.P = b->par;
-    hipLaunchKernelGGL(hrm::k_set_int, dim3(1), dim3(64), 0, s, b->d_queue, 0);
+    hipLaunchKernelGGL(hrm::k_reset_queue, dim3(1), dim3(64), 0, s, b->d_queue);
     int rc = b->N == 2 ? launch_n<2>(b, A, s) : launch_n<3>(b, A, s);
     if (rc != HRM_OK) return rc;
     const hipError_t e = hipGetLastError();
@@ -348,23 +371,35 @@ int hrm_batch_create(const hrm_eos* e, const hrm_params* prm, int nprob, const l
     P.flags = 0;
     P.fast_flux_limiter = p.eps_f_ar >= p.hs_f_ar && p.eps_f_a >= p.hs_f_a && p.eps_f_re >= p.hs_f_re;
     P.fast_interp_limiter = p.eps_i_ar >= p.hs_i_ar && p.eps_i_a >= p.hs_i_a;
-    // default launch: 256 threads, three workgroups per CU (the kernel's
-    // register budget admits three waves per SIMD), 10 steps per launch
+    // default launch, 10 steps each.  Up to two problems per CU, one of them longer
+    // than a tile: a workgroup for each, 512 threads wide except `narrow` of them
+    // (the short problems, and as many more as keep one wide one per CU).  Beyond
+    // that the narrow tiles waste less: three workgroups of 256 threads per CU (the
+    // register budget admits three waves per SIMD; us a step, 1000 problems of
+    // 200-600 cells 88 against 97 mixed, 4096 of 200-2000 640 against 743).
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         cus = 256;
     (void)hipGetLastError();
-    b->threads = 256;
-    b->blocks = 3 * cus;
-    b->ksteps = 10;
-
     // longest problems first
     std::vector<int> order(nprob);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
         return h_offsets[x + 1] - h_offsets[x] > h_offsets[y + 1] - h_offsets[y];
     });
+    const int nshort = (int)std::count_if(order.begin(), order.end(),
+                                          [&](int x) { return h_offsets[x + 1] - h_offsets[x] < 256; });
+    if (nprob <= 2 * cus && nshort < nprob) {
+        b->threads = 512;
+        b->narrow = std::min(cus, std::max(nshort, nprob - cus));
+        b->blocks = nprob;
+    } else {
+        b->threads = 256;
+        b->blocks = 3 * cus;
+    }
+    b->ksteps = 10;
+
     const size_t bytes = sizeof(double) * (size_t)b->M * (size_t)b->T;
     bool ok = hipMalloc((void**)&b->d_W1, bytes) == hipSuccess;
     ok = ok && hipMalloc((void**)&b->d_W2, bytes) == hipSuccess;
@@ -373,7 +408,7 @@ int hrm_batch_create(const hrm_eos* e, const hrm_params* prm, int nprob, const l
     ok = ok && hipMalloc((void**)&b->d_order, sizeof(int) * nprob) == hipSuccess;
     ok = ok && hipMalloc((void**)&b->d_t, sizeof(double) * nprob) == hipSuccess;
     ok = ok && hipMalloc((void**)&b->d_tend, sizeof(double) * nprob) == hipSuccess;
-    ok = ok && hipMalloc((void**)&b->d_queue, sizeof(int)) == hipSuccess;
+    ok = ok && hipMalloc((void**)&b->d_queue, sizeof(int) * 3) == hipSuccess;
     ok = ok && hipMalloc((void**)&b->d_cnt, sizeof(unsigned long long) * 8) == hipSuccess;
     ok = ok && hipMemcpy(b->d_off, h_offsets, sizeof(long long) * (nprob + 1), hipMemcpyHostToDevice) == hipSuccess;
     ok = ok && hipMemcpy(b->d_dx, h_dx, sizeof(double) * nprob, hipMemcpyHostToDevice) == hipSuccess;

@@ -840,10 +840,10 @@ __device__ inline void flush_counters(unsigned packed, unsigned long long* dst)
 // NaN-propagating max (a NaN anywhere makes the result NaN)
 __device__ inline double nmax(double a, double b) { return a != a ? a : (b != b ? b : fmax(a, b)); }
 
-// block-wide max of D values (blockDim.x a multiple of 64, <= 256); the
-// result is valid in thread 0; sh holds >= 4 * D doubles
+// block-wide max of D values over the bs threads of the workgroup (a multiple of
+// 64); the result is valid in thread 0; sh holds >= bs / 64 * D doubles
 template <int D>
-__device__ inline void block_max(double* m, double* sh)
+__device__ inline void block_max(double* m, double* sh, int bs = (int)blockDim.x)
 {
 #pragma unroll
     for (int d = 0; d < D; ++d)
@@ -855,7 +855,7 @@ __device__ inline void block_max(double* m, double* sh)
         for (int d = 0; d < D; ++d) sh[w * D + d] = m[d];
     __syncthreads();
     if (threadIdx.x == 0)
-        for (int i = 1; i < (int)(blockDim.x >> 6); ++i)
+        for (int i = 1; i < bs >> 6; ++i)
 #pragma unroll
             for (int d = 0; d < D; ++d) m[d] = nmax(m[d], sh[i * D + d]);
 }

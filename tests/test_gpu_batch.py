@@ -220,3 +220,42 @@ def test_fp32_ensemble_positivity(H, I):
     assert d["relax_bad"] == 0, d
     assert w[:N].min() > 0.0
     assert w[N + 2:].min() > 0.0 and w[N + 2:].max() < 1.0
+
+
+@pytest.mark.parametrize("nprob,nmin,nmax,species,precision", [
+    (18, 1, 700, 2, "FP64"), (5, 256, 1100, 2, "FP64"), (300, 240, 300, 2, "FP64"), (300, 240, 300, 2, "FP32"),
+    (24, 250, 520, 3, "FP64"), (24, 250, 520, 3, "FP32"), (530, 30, 60, 2, "FP64")])
+def test_default_launch_keeps_the_bits(H, I, nprob, nmin, nmax, species, precision):
+    """The default launch of few problems (wide and narrow workgroups side by
+    side) against a configured one: every bit, time and count, also where some
+    problems stop at their end time."""
+    import torch
+    rng = np.random.default_rng(nprob + nmax)
+    lens = EDGE_LENGTHS if nprob == 18 else rng.integers(nmin, nmax + 1, size=nprob)
+    batch = I.config4(lengths=lens, seed=4106)
+    if species == 3:
+        eos = I.eos_of(I.LIQ_B, I.AIR, I.HELIUM)
+        batch = I.Batch("three", eos, I.random_admissible(eos, 1, batch.ncell, seed=7), batch.offsets, batch.dx)
+    outs = []
+    for shape in ((256, 512, 10), None):
+        s = H.BatchSolver(batch, precision=getattr(H, precision))
+        if shape:
+            s.configure(*shape)
+        if outs:  # every third problem stops halfway through the first run's time
+            ends = np.where(np.arange(nprob) % 3 == 0, 0.5 * outs[0][1], 0.0)
+        else:
+            s.run(10)
+            outs.append((s.state(), s.times()))
+            s.close()
+            s = H.BatchSolver(batch, precision=getattr(H, precision))
+            s.configure(*shape)
+            ends = np.where(np.arange(nprob) % 3 == 0, 0.5 * outs[0][1], 0.0)
+        H.hrm_batch_set_end_times(s.b, ends)
+        s.run(20)
+        torch.cuda.synchronize()
+        outs.append((s.state(), s.times(), s.diagnostics()))
+        s.close()
+    _, ref, got = outs
+    assert np.array_equal(ref[0], got[0], equal_nan=True)
+    assert np.array_equal(ref[1], got[1], equal_nan=True)
+    assert ref[2] == got[2]
