@@ -192,7 +192,7 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
     if constexpr (sizeof(R) == sizeof(double))
         irc = rcp_newton(rb * cb);
     else
-        irc = (R)1 / (rb * cb);
+        irc = div_rn((R)1, rb * cb);
     const R irc2 = irc * irc * rb;
     const ParDev Pw = kload<ParDev>(kp);
     const double eps = Pw.eps_weno;
