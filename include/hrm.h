@@ -312,7 +312,7 @@ int hrm_mlp_adam(float* d_params, const float* d_grad, float* d_m, float* d_v, i
  * time slot[4] advanced and clipped to t_end), then runs three stages with
  * the context's stage buffers, relaxing each stage's output.  The maxima of
  * the first step are taken by a pass over d_W; those of every later step
- * by the last sweep of the step before, from the cells it has just written
+ * by the last launch of the step before, from the cells it has just written
  * (the same values, so the result equals nsteps calls of hrm_step to the
  * bit).  d_W (M x ncell, component-major) and d_slot (>= 5 doubles) are the
  * caller's device memory; nothing else in d_W may change during the call.
@@ -320,6 +320,9 @@ int hrm_mlp_adam(float* d_params, const float* d_grad, float* d_m, float* d_v, i
  * are captured once into a hipGraph on a private stream and replayed on
  * `stream` for every step with the same (d_W, d_slot, cfl, dt_fixed,
  * t_end); other arguments re-capture.  The graph holds kernel nodes only.
+ * Lines (dim 1) with the App. C weights, or of the first-order schemes, take no
+ * graph up to 307200 cells (unless timing is on): all steps in one launch on
+ * `stream` up to a few hundred cells, else one launch to set up and one per step.
  * HRM_EINVAL for NULL pointers, nsteps < 0, or neither cfl nor dt_fixed
  * positive; nsteps == 0 launches nothing. */
 int hrm_advance(hrm_ctx* ctx, double* d_W, int nsteps, double cfl, double dt_fixed, double t_end, double* d_slot,

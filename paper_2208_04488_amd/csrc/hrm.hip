@@ -1259,6 +1259,7 @@ int hrm_create(const hrm_grid* g, const hrm_eos* e, const hrm_params* prm, hrm_c
         while (c->nslot < 2048 && 2ll * c->nslot <= nblk) c->nslot *= 2;
     }
     int nparts = std::max(c->npart, c->nslot);
+    if (c->D == 1) nparts = (int)std::max<long long>(nparts, (hrm::line_part(c->ncell) + 2) / 3);
     for (int d = 0; d < 3; ++d) {
         c->nface[d] = c->ncell / c->n[d];
         c->nbpart[d] = (int)std::min<long long>((c->nface[d] + 255) / 256, 256);
@@ -1443,9 +1444,9 @@ int hrm_advance(hrm_ctx* c, double* d_W, int nsteps, double cfl, double dt_fixed
     if (nsteps == 0) return HRM_OK;
     hipStream_t s = (hipStream_t)stream;
     c->last_stream = s;
-    // a line that one workgroup holds: all steps in one launch (the launch
-    // timers want the sweeps one by one)
-    if (c->D == 1 && !c->timing_mask && c->n[0] <= hrm::line_cells(c->par.flags, c->precision, c->weights)) {
+    // a line: a step, or all of them where one workgroup holds it, in one launch
+    // (the launch timers want the sweeps one by one)
+    if (c->D == 1 && !c->timing_mask && hrm::line_fits(c->n[0], c->par.flags, c->precision, c->weights)) {
         if (const int rb = check_boundary(c)) return rb;
         hrm::LineArgs A;
         memset(&A, 0, sizeof(A));
@@ -1462,7 +1463,10 @@ int hrm_advance(hrm_ctx* c, double* d_W, int nsteps, double cfl, double dt_fixed
         A.dt = dt_args(c, cfl, dt_fixed, t_end);
         A.e = c->eos;
         A.P = c->par;
-        hrm::line_launch(c->N, c->precision, A, s);
+        if (c->n[0] <= hrm::line_cells(c->N, c->par.flags, c->precision))
+            hrm::line_launch(c->N, c->precision, A, s);
+        else
+            hrm::line_steps(c->N, c->precision, A, c->d_W1, c->d_part, s);
         return check_launch(c, "hrm_advance line");
     }
     int rc = seed_enqueue(c, d_W, s);

@@ -14,16 +14,13 @@ inline bool line_first_order(int flags, int precision)
 }
 
 // Cells of the longest line that one workgroup advances, a face per thread.
-// Up to 511 it beats a launch per sweep on several CUs at every scheme.  From
-// 512 on the four SIMDs of one CU have four waves of faces each and are
-// slower than several CUs for the high-order scheme (two species, a step: 29
-// against 35 us at 400 cells, 38 against 35 at 700), but not for the
-// first-order schemes, whose faces are a tenth of the work (four equations: 16
-// against 25 us at 1023).
-inline int line_cells(int flags, int precision, int weights)
+// Beyond, a launch per step on several CUs with one wave of faces on a SIMD is
+// faster than two on each of one CU's (us a step, this against those: high order,
+// two species, 447 cells 21.3 / 25.0, 480 26.7 / 24.5; three species, 320 cells 30.5
+// / 35.1, 447 38.1 / 35.7; four equations, 511 cells 10.0 / 11.9, 600 13.5 / 12.0).
+inline int line_cells(int N, int flags, int precision)
 {
-    if (line_first_order(flags, precision)) return 1023;
-    return weights == HRM_WEIGHTS_IS ? 511 : 0;
+    return line_first_order(flags, precision) ? 511 : (N == 2 ? 447 : 383);
 }
 
 struct LineArgs {
@@ -40,7 +37,36 @@ struct LineArgs {
     ParDev P;
 };
 
-// N = 2 or 3, 1 <= A.n <= line_cells()
+// N = 2 or 3, 1 <= A.n <= line_cells(N, ...)
 void line_launch(int N, int precision, const LineArgs& A, hipStream_t s);
+
+// the steps of a longer line, a launch each, in tiles of LINE_BS threads
+constexpr int LINE_BS = 256;
+
+// Lines advanced without the sweeps: up to where the tiles fill the chip and their
+// halos cost more than the launches (us a step, a launch each against three sweeps:
+// 5000 cells 23.6 / 31.7, 120000 32.4 / 42.0, 300000 54.7 / 62.9; three species,
+// 600000 139.5 / 136.0).  The learned weights are left to the sweeps.
+inline bool line_fits(int n, int flags, int precision, int weights)
+{
+    return n <= 1200 * LINE_BS && (line_first_order(flags, precision) || weights == HRM_WEIGHTS_IS);
+}
+
+// doubles of `part` (wavespeeds of two steps and the time) for n cells
+inline long long line_part(long long n) { return 2 * (n / (LINE_BS / 2) + 2) + 2; }
+
+struct LineStepArgs {
+    LineArgs a;  // first: line_nodes and line_update find its members there
+    const double* src;
+    double* dst;
+    const double* pin;  // wavespeeds of src, by tile
+    double* pout;       // those of dst (null after the last step)
+    const double* tin;
+    double* tout;
+    int own, npart;
+};
+
+// N = 2 or 3, line_fits(A.n, ...); other: as many doubles as the state
+void line_steps(int N, int precision, const LineArgs& A, double* other, double* part, hipStream_t s);
 
 }  // namespace hrm

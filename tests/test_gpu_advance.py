@@ -270,7 +270,7 @@ def test_advance_zero_steps_and_errors(H):
     s.close()
 
 
-# lines one workgroup advances (k_line: up to 511 cells, first order 1023) at the
+# lines one workgroup advances (k_line: up to 447 cells, 511 at first order) at the
 # edges of its block sizes, and the first ones beyond
 @pytest.mark.parametrize("n", [1, 2, 3, 63, 64, 255, 256, 511, 512, 1023, 1024])
 @pytest.mark.parametrize("kind", ["open", "periodic", "dirichlet", "three", "fp32", "first", "four_eq"])
@@ -308,6 +308,54 @@ def test_short_line_against_stages(H, n, kind):
     assert err <= tol
     assert np.allclose(a.slot[:5].cpu().numpy(), b.slot[:5].cpu().numpy(), rtol=tol, atol=0)
     if kind != "fp32":
+        assert da == db
+    a.close()
+    b.close()
+
+
+# lines advanced by a launch per step (k_line_step): whole tiles of 237 cells (249
+# at first order) and one cell more, an odd and an even number of steps
+@pytest.mark.parametrize("n,steps", [(711, 1), (712, 2), (1185, 3), (1245, 2), (1246, 3), (5000, 2)])
+@pytest.mark.parametrize("kind", ["open", "periodic", "dirichlet", "three", "fp32", "first", "four_eq", "ends"])
+def test_long_line_against_stages(H, n, steps, kind):
+    """hrm_advance on a line against the caller's own loop of wavespeed, time
+    step and stages, to the bars of the short line, 1e-11 a step (1e-6 in
+    float); "ends": the end time falls into the last step, and one more is held."""
+    import torch
+    flags = H.FUSE_RELAX | {"first": H.FIRST_ORDER, "four_eq": H.FOUR_EQ}.get(kind, 0)
+    prec = H.FP32 if kind == "fp32" else H.FP64
+    base = I.shock_interface(n) if kind == "three" else I.config1(n)
+    bc = {"periodic": (I.PERIODIC, I.PERIODIC), "dirichlet": (I.DIRICHLET, I.TRANSMISSIVE)}.get(kind, (0, 0))
+    prob = I.Problem(base.name, base.eos, 1, base.n, base.dx, [bc], base.W, cfl=0.4)
+    if kind == "dirichlet":
+        prob.boundary = {(0, 0): np.ascontiguousarray(base.W[:, 0, 0, :1])}
+    a, b = (H.Solver(prob, flags=flags, precision=prec) for _ in range(2))
+    t_end = 0.0
+    if kind == "ends":
+        b.compute_dt(0.4) if b.wavespeed() is not None else None
+        t_end = (steps - 0.5) * float(b.slot[0])
+        b.slot.zero_()
+        steps += 1
+    a.advance(steps, cfl=0.4, t_end=t_end)
+    for _ in range(steps):
+        b.wavespeed()
+        b.compute_dt(0.4, t_end=t_end)
+        w1 = b.stage(0, b.W, b.W)
+        w2 = b.stage(1, b.W, w1)
+        b.W.copy_(b.stage(2, b.W, w2))
+    torch.cuda.synchronize()
+    da, db = a.diagnostics(), b.diagnostics()
+    got, ref = a.state(), b.state()
+    N, M = prob.N, prob.M
+    scale = np.abs(ref.reshape(M, -1)).max(axis=1)
+    scale[N] = ref[:N].sum(0).max() * b.wavespeed().max()
+    scale[N + 2:] = 1.0
+    err = (np.abs(got - ref).reshape(M, -1).max(axis=1) / scale).max()
+    tol = steps * (1e-6 if kind == "fp32" else 1e-11)
+    assert err <= tol
+    sa, sb = a.slot[:5].cpu().numpy(), b.slot[:5].cpu().numpy()
+    assert np.allclose(sa, sb, rtol=tol, atol=tol * sb[4])
+    if kind not in ("fp32", "ends"):
         assert da == db
     a.close()
     b.close()
