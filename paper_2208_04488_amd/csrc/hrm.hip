@@ -476,6 +476,149 @@ __global__ void __launch_bounds__(BS* BA, (sweep_waves<D, DIR, R, WT>())) k_swee
     flush_counters(cnt, A.cnt);
 }
 
+// A stage of a small 2D grid, both directions of a tile of 15 x 7 cells in one
+// launch: waves 0 and 1 take its 16 x 7 faces along x, waves 2 and 3 its 15 x 8
+// along y, and the cells add both differences in the order of the two sweeps
+// (the same bits).  A sweep of such a grid is bound by the latency of one wave
+// of faces on a SIMD and by its launch, and this takes one of each instead of
+// two and no pass through the right-hand side (127 x 65, two species, a stage
+// 19.3 -> 10.7 us); the tile computes 2.21 faces a cell and stages 2.26 nodes, so
+// larger grids, which are bound by issue, are left to the sweeps.
+struct PlaneArgs {
+    SweepArgs s;  // first: its members are read through the argument pointer; x sides
+    int bclo, bchi;
+    const double* blo;
+    const double* bhi;
+    double idx;
+};
+constexpr int PLANE_X = 15, PLANE_Y = 7;
+
+template <int N, typename R>
+__global__ void __launch_bounds__(256, 2) k_plane(const PlaneArgs A)
+{
+    using F = NodeFields<N, 2>;
+    constexpr int D = 2, M = 2 * N + D, IA = N + D + 1;
+    constexpr int NA = N > 1 ? N - 1 : 1;
+    constexpr int LX = PLANE_X + 6, FS = LX * (PLANE_Y + 6), XF = 128;  // the y faces' slots start at XF
+    static_assert(PLANE_X + 1 == 16 && 16 * PLANE_Y <= XF && PLANE_X * (PLANE_Y + 1) <= 256 - XF && FS >= 256, "tile");
+    // the node tile without its corners: halo rows of PLANE_X nodes, whole rows of LX
+    constexpr int HALO = 3 * PLANE_X, ROWS = LX * PLANE_Y;
+    static_assert(2 * HALO + ROWS <= 256, "one node a thread");
+    __shared__ double lds[F::COUNT * FS];
+    const int tid = threadIdx.x;
+    const int n0 = A.s.n[0], n1 = A.s.n[1], x0 = blockIdx.x * PLANE_X, y0 = blockIdx.y * PLANE_Y;
+    const int nx = min(PLANE_X, n0 - x0), ny = min(PLANE_Y, n1 - y0);  // cells of the tile
+    const long long nc = A.s.ncell;
+
+    if (tid < 2 * HALO + ROWS) {
+        int lx, ly;
+        if (tid < HALO) {
+            ly = tid / PLANE_X;
+            lx = 3 + tid % PLANE_X;
+        } else if (tid < HALO + ROWS) {
+            ly = 3 + (tid - HALO) / LX;
+            lx = (tid - HALO) % LX;
+        } else {
+            ly = 3 + PLANE_Y + (tid - HALO - ROWS) / PLANE_X;
+            lx = 3 + (tid - HALO - ROWS) % PLANE_X;
+        }
+        const int gx = x0 - 3 + lx, gy = y0 - 3 + ly;
+        const int cx = map_bc(gx, n0, A.s.bclo, A.s.bchi), cy = map_bc(gy, n1, A.bclo, A.bchi);
+        const double* src = A.s.Ws;
+        long long idx = (long long)cy * n0 + cx, stride = nc;
+        // Dirichlet: every ghost node takes the boundary state of its line
+        if ((gx < 0 && A.s.bclo == BC_DIRICHLET) || (gx >= n0 && A.s.bchi == BC_DIRICHLET)) {
+            src = gx < 0 ? A.s.blo : A.s.bhi;
+            idx = cy;
+            stride = n1;
+        } else if ((gy < 0 && A.bclo == BC_DIRICHLET) || (gy >= n1 && A.bchi == BC_DIRICHLET)) {
+            src = gy < 0 ? A.blo : A.bhi;
+            idx = cx;
+            stride = n0;
+        }
+        double w[M];
+#pragma unroll
+        for (int c = 0; c < M; ++c) w[c] = src[c * stride + idx];
+        const EosDev e = kload<EosDev>(kernel_args() + offsetof(SweepArgs, e));
+        St<N, D> s;
+        state_from_W<N, D>(e, w, s);
+        const int b = ly * LX + lx;
+#pragma unroll
+        for (int c = 0; c < M; ++c) lds[c * FS + b] = w[c];
+#pragma unroll
+        for (int d = 0; d < D; ++d) lds[(F::U + d) * FS + b] = s.u[d];
+        lds[F::P * FS + b] = s.p;
+        lds[F::RHO * FS + b] = s.rho;
+        lds[F::C * FS + b] = s.c;
+    }
+    __syncthreads();
+
+    // faces; lanes without one repeat the last of their direction, and a face
+    // between two tiles is counted by the upper one
+    double G[M], Gp[NA];
+    unsigned cnt = 0, lc = 0;
+    constexpr int LOW = sizeof(R) == sizeof(double) ? 0 : 1;
+    if (__builtin_amdgcn_readfirstlane(tid) < XF) {
+        const int fx = tid % 16, fy = tid / 16, qx = min(fx, nx), qy = min(fy, ny - 1);
+        face_flux<N, D, 0, 1, FS, R, 0, LOW>(lds + (qy + 3) * LX + qx, kernel_args() + offsetof(SweepArgs, e),
+                                             kernel_args() + offsetof(SweepArgs, P), A.s.slot[1], G, Gp, lc);
+        if (fy < ny && (fx < nx || x0 + fx == n0) && (fx < PLANE_X || x0 + fx == n0)) cnt = lc;
+    } else {
+        const int f = tid - XF, fx = f % PLANE_X, fy = f / PLANE_X, qx = min(fx, nx - 1), qy = min(fy, ny);
+        face_flux<N, D, 1, LX, FS, R, 0, LOW>(lds + qy * LX + qx + 3, kernel_args() + offsetof(SweepArgs, e),
+                                              kernel_args() + offsetof(SweepArgs, P), A.s.slot[2], G, Gp, lc);
+        if (fx < nx && fy <= PLANE_Y && (fy < ny || y0 + fy == n1) && (fy < PLANE_Y || y0 + fy == n1)) cnt = lc;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < M; ++c) lds[c * FS + tid] = G[c];
+#pragma unroll
+    for (int k = 0; k < N - 1; ++k) lds[(M + k) * FS + tid] = Gp[k];
+    __syncthreads();
+
+    const int ci = tid % PLANE_X, cj = tid / PLANE_X;
+    double wmax[D] = {0.0, 0.0};
+    if (ci < nx && cj < ny) {
+        const long long cell = (long long)(y0 + cj) * n0 + x0 + ci;
+        const int bx = cj * 16 + ci, by = XF + cj * PLANE_X + ci;
+        const double dt = A.s.slot[0];
+        double w[M];
+        if (__builtin_expect(A.s.hold && dt == 0.0, 0)) {
+#pragma unroll
+            for (int c = 0; c < M; ++c) w[c] = A.s.Wn[c * nc + cell];
+        } else {
+#pragma unroll
+            for (int c = 0; c < M; ++c) {
+                const int m = c >= IA ? M + c - IA : c;  // the pair's slots of the volume fractions
+                const double Lx = -(lds[c * FS + bx + 1] - lds[m * FS + bx]) * A.s.idx;
+                const double Ly = -(lds[c * FS + by + PLANE_X] - lds[m * FS + by]) * A.idx;
+                w[c] = A.s.a * A.s.Wn[c * nc + cell] + A.s.b * (A.s.Ws[c * nc + cell] + dt * (Lx + Ly));
+            }
+            if (A.s.relax && !relax_cell<N, D>(kload<EosDev>(kernel_args() + offsetof(SweepArgs, e)), w)) cnt += cnt_one(C_RELAX_BAD);
+        }
+#pragma unroll
+        for (int c = 0; c < M; ++c) A.s.Wout[c * nc + cell] = w[c];
+        if (A.s.wpart) {
+            St<N, D> s;
+            state_from_W<N, D>(kload<EosDev>(kernel_args() + offsetof(SweepArgs, e)), w, s);
+#pragma unroll
+            for (int d = 0; d < D; ++d) wmax[d] = fabs(s.u[d]) + s.c;
+        }
+    }
+    if (A.s.wpart) {
+        unsigned long long wb[D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) wb[d] = wave_umax64((unsigned long long)__double_as_longlong(wmax[d]));
+        if ((tid & 63) == 0) {
+            const unsigned blk = blockIdx.x + gridDim.x * blockIdx.y;
+            unsigned long long* slot = (unsigned long long*)A.s.wpart + (blk & (A.s.nslot - 1u)) * D;
+#pragma unroll
+            for (int d = 0; d < D; ++d) atomicMax(slot + d, wb[d]);
+        }
+    }
+    flush_counters(cnt, A.s.cnt);
+}
+
 // The pointwise kernels are bound by memory.  V cells per thread: two, with
 // 16-byte loads and stores, where every plane of every array is aligned for
 // them (an even number of cells and 16-byte pointers), else one.
@@ -917,6 +1060,31 @@ struct Ops {
         }
     }
 
+    // a stage by k_plane
+    static void plane(hrm_ctx* c, const hrm::SweepArgs& S, hipStream_t s)
+    {
+        if constexpr (D == 2) {
+            hrm::PlaneArgs A;
+            memset(&A, 0, sizeof(A));
+            A.s = S;
+            A.s.bclo = c->bclo[0];
+            A.s.bchi = c->bchi[0];
+            A.s.blo = c->d_bnd[0][0];
+            A.s.bhi = c->d_bnd[0][1];
+            A.s.idx = 1.0 / c->dx[0];
+            A.bclo = c->bclo[1];
+            A.bchi = c->bchi[1];
+            A.blo = c->d_bnd[1][0];
+            A.bhi = c->d_bnd[1][1];
+            A.idx = 1.0 / c->dx[1];
+            const dim3 grd((c->n[0] + hrm::PLANE_X - 1) / hrm::PLANE_X, (c->n[1] + hrm::PLANE_Y - 1) / hrm::PLANE_Y);
+            if (c->precision == HRM_FP32)
+                hipLaunchKernelGGL((hrm::k_plane<N, float>), grd, dim3(256), 0, s, A);
+            else
+                hipLaunchKernelGGL((hrm::k_plane<N, double>), grd, dim3(256), 0, s, A);
+        }
+    }
+
     // two cells per thread of a pointwise kernel: planes of nc doubles at 16-byte
     // addresses throughout
     static bool pairs(long long nc, std::initializer_list<const void*> arrays)
@@ -1026,6 +1194,20 @@ hrm::SweepArgs base_args(hrm_ctx* c)
 
 int check_boundary(hrm_ctx* c);
 
+// The stages that k_plane takes: of 2D grids of up to 2048 tiles (eight a CU,
+// 215 000 cells), where it beats the two sweeps (us a step, sweeps / k_plane, two
+// species: 127 x 65 62 / 36, 300 x 200 78 / 62, 500 x 300 114 / 94, 700 x 350 144 / 131,
+// 1024 x 512 211 / 231; three species: 76 / 43, 93 / 74, 135 / 119, 175 / 169, 255 / 294).
+// The first-order schemes, the learned weights and runs with the launch timers on,
+// which want the sweeps one by one, are left to the sweeps.
+bool plane_fits(const hrm_ctx* c)
+{
+    const long long tiles =
+        ((c->n[0] + hrm::PLANE_X - 1ll) / hrm::PLANE_X) * ((c->n[1] + hrm::PLANE_Y - 1ll) / hrm::PLANE_Y);
+    return c->D == 2 && tiles <= 2048 && c->weights == HRM_WEIGHTS_IS &&
+           !(c->flags & (HRM_FIRST_ORDER | HRM_FOUR_EQ)) && !c->timing_mask;
+}
+
 // all directions of L(W_s); with `stage` the last one applies the stage
 // update (and writes the wavespeed partials of its output into wpart)
 int run_operator(hrm_ctx* c, const double* Ws, const double* Wn, double* Wout, double* rhs, const double* slot,
@@ -1058,6 +1240,10 @@ int run_operator(hrm_ctx* c, const double* Ws, const double* Wn, double* Wout, d
         A.dt = *dt;
     }
     int rc = HRM_OK;
+    if (stage && plane_fits(c)) {
+        rc = dispatch(c, [&](auto ops) { decltype(ops)::plane(c, A, s); });
+        return rc != HRM_OK ? rc : check_launch(c, "stage");
+    }
     for (int d = 0; d < c->D; ++d) {
         const bool last = d == c->D - 1;
         A.mode = (stage && last) ? hrm::MODE_FINAL : (d == 0 ? hrm::MODE_WRITE : hrm::MODE_ADD);

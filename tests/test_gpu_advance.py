@@ -359,3 +359,46 @@ def test_long_line_against_stages(H, n, steps, kind):
         assert da == db
     a.close()
     b.close()
+
+
+# small 2D grids, both directions of a 15 x 7 tile in one launch (k_plane): whole
+# tiles, one cell more and one less, grids narrower than a stencil, the largest
+# number of tiles and one more; against the sweeps, which the launch timers select
+@pytest.mark.parametrize("n", [(1, 1), (2, 9), (14, 6), (15, 7), (16, 8), (30, 14), (127, 65), (480, 448), (481, 448)])
+@pytest.mark.parametrize("kind", ["open", "periodic", "inflow", "three", "fp32"])
+def test_small_plane_against_sweeps(H, n, kind):
+    """Two steps either way, to 1e-11 a step (1e-6 in float) of each component's
+    scale; every count equal in double."""
+    import torch
+    N = 3 if kind == "three" else 2
+    eos = I.eos_of(I.LIQ_A, I.AIR, I.HELIUM) if N == 3 else I.eos_of(I.LIQ_A, I.AIR)
+    x, y = np.meshgrid((np.arange(n[0]) + 0.5) / n[0], (np.arange(n[1]) + 0.5) / n[1])
+    wave = 0.5 * (np.cos(2 * np.pi * x) + np.cos(4 * np.pi * y + 1))
+    liq = I.TRACE + (1 - 4 * I.TRACE) * 0.5 * (1 + np.tanh((wave - 0.3) * 12))
+    alpha = [liq, 1 - liq] if N == 2 else [liq, 0.3 * (1 - liq), 0.7 * (1 - liq)]
+    u = [30.0 * np.sin(2 * np.pi * x), 20.0 * np.sin(2 * np.pi * y + 1)]
+    W = I.equilibrium_state(eos, alpha, u, 1e5 * (1 + 0.2 * wave), 300.0 + 20 * wave)
+    W = np.ascontiguousarray(W.reshape((W.shape[0], 1, n[1], n[0])))
+    bc = {"periodic": [(I.PERIODIC,) * 2] * 2, "inflow": [(I.DIRICHLET, 0), (0, I.DIRICHLET)]}.get(kind, [(0, 0)] * 2)
+    prob = I.Problem("plane", eos, 2, n, (1.0 / max(n),) * 2, bc, W)
+    if kind == "inflow":
+        prob.boundary = {(0, 0): np.ascontiguousarray(W[:, :, :, 0]), (1, 1): np.ascontiguousarray(W[:, :, -1, :])}
+    prec = H.FP32 if kind == "fp32" else H.FP64
+    a, b = (H.Solver(prob, flags=H.FUSE_RELAX, precision=prec) for _ in range(2))
+    H.hrm_set_timing(b.ctx, 1)
+    for s in (a, b):
+        s.advance(2, cfl=0.4)
+    torch.cuda.synchronize()
+    got, ref = (s.state().reshape(prob.M, -1) for s in (a, b))
+    scale = np.abs(ref).max(axis=1)
+    scale[N:N + 2] = ref[:N].sum(0).max() * b.wavespeed().max()
+    scale[N + 3:] = 1.0
+    tol = 2 * (1e-6 if kind == "fp32" else 1e-11)
+    err = (np.abs(got - ref).max(axis=1) / scale).max()
+    print(n, kind, "k_plane against the sweeps: %.1e" % err)
+    assert err <= tol
+    assert np.allclose(a.slot[:5].cpu().numpy(), b.slot[:5].cpu().numpy(), rtol=tol, atol=0)
+    if kind != "fp32":
+        assert a.diagnostics() == b.diagnostics()
+    a.close()
+    b.close()
