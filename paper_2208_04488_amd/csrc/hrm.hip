@@ -13,6 +13,7 @@
 //                     last stage of a step it also folds the block maxima
 //                     of |u_d| + c of the new state into the partial slots
 //                     of the next step's time step.
+//   k_plane           a stage of a small 2D grid, both directions of a tile.
 //   k_relax           point-wise relaxation.
 //   k_wavespeed       per-block max of |u_d| + c (the first step of a run,
 //                     hrm_max_wavespeed), then k_reduce_max / k_reduce_dt
