@@ -170,10 +170,25 @@ __device__ inline float div_rn(float a, float b)
     return fmaf(fmaf(-b, q, a), r, q);
 }
 
+// x_0^2 + ... + x_{D-1}^2 in one written order; of x_0 and x_1, LAST is the one
+// whose square is not rounded
+template <int D, typename R, int LAST = 0>
+__device__ inline R sum_of_squares(const R* x)
+{
+#pragma clang fp contract(off)
+    if constexpr (D == 1) return x[0] * x[0];
+    R s = fma(x[LAST], x[LAST], x[1 - LAST] * x[1 - LAST]);
+    if constexpr (D == 3) s = fma(x[2], x[2], s);
+    return s;
+}
+
 // conservative W[M] -> full state (hot-path step a1).  The multiply-adds are
 // written out and no others formed, so that every kernel that takes |u| + c of
-// a cell (the separate pass, the sweep that wrote it, the line) gets the same
-// bits, and with them the same time step.
+// a cell (the separate pass, the sweep that wrote it, the line, the ensemble)
+// gets the same bits, and with them the same time step.  The order is kept:
+// with rho c^2 off by its last bit 3 to 5 % of an ensemble's time steps were off
+// by theirs, which float faces turned into 1e-7 to 1e-5 of the momentum of single
+// cells after ten steps.
 template <int N, int D>
 __device__ inline void state_from_W(const EosDev& e, const double* W, St<N, D>& s)
 {
@@ -195,12 +210,11 @@ __device__ inline void state_from_W(const EosDev& e, const double* W, St<N, D>& 
     }
     s.al[N - 1] = 1.0 - asum;
     const double irho = rcp_newton(rho);
-    double m2 = W[N] * W[N];
+    const double m2 = sum_of_squares<D>(W + N);
 #pragma unroll
     for (int d = 0; d < D; ++d) {
         s.mom[d] = W[N + d];
         s.u[d] = W[N + d] * irho;
-        if (d > 0) m2 = fma(W[N + d], W[N + d], m2);
     }
     double Gam, Pi;
     mixture<N>(e, s.al, Gam, Pi);
@@ -208,22 +222,23 @@ __device__ inline void state_from_W(const EosDev& e, const double* W, St<N, D>& 
     s.E = W[IE];
     const double re = fma(-0.5 * m2, irho, W[IE]) - rq;
     s.p = (re - Pi) * iG;
-    s.rc2 = fma(s.p + Pi, iG, s.p);
+    s.rc2 = fma(fma(re - Pi, iG, Pi), iG, s.p);
     s.rho = rho;
     const double c2 = s.rc2 * irho;
     s.c = c2 == 0.0 ? 0.0 : sqrt_rn(c2);
 }
 
 // primitive slots (ar, u, p, al[0..N-2]) already set -> the rest of the state
-template <int N, int D, typename R>
+template <int N, int D, typename R, int DIR = 0>
 __device__ inline void complete_from_prim(const EosDev& e, St<N, D, R>& s)
 {
+#pragma clang fp contract(off)
     R rho = 0, rq = 0;
     double asum = 0.0;
 #pragma unroll
     for (int k = 0; k < N; ++k) {
         rho += s.ar[k];
-        rq += s.ar[k] * (R)e.q[k];
+        rq = fma(s.ar[k], (R)e.q[k], rq);
     }
 #pragma unroll
     for (int k = 0; k < N - 1; ++k) asum += s.al[k];
@@ -231,14 +246,11 @@ __device__ inline void complete_from_prim(const EosDev& e, St<N, D, R>& s)
     double Gd, Pd;
     mixture<N>(e, s.al, Gd, Pd);
     const R Gam = (R)Gd, Pi = (R)Pd;
-    R u2 = 0;
+    const R u2 = sum_of_squares<D, R, DIR == 1>(s.u);
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-        s.mom[d] = rho * s.u[d];
-        u2 += s.u[d] * s.u[d];
-    }
+    for (int d = 0; d < D; ++d) s.mom[d] = rho * s.u[d];
     s.rho = rho;
-    s.E = Gam * s.p + Pi + (R)0.5 * rho * u2 + rq;
+    s.E = fma((R)0.5 * rho, u2, fma(Gam, s.p, Pi)) + rq;
     s.rc2 = s.p + div_rn(s.p + Pi, Gam);
     s.c = sqrt_rn(div_rn(s.rc2, rho));
 }
@@ -247,15 +259,14 @@ __device__ inline void complete_from_prim(const EosDev& e, St<N, D, R>& s)
 template <int N, int D>
 __device__ inline double rhoe_tilde(const EosDev& e, const double* W)
 {
-    double rho = 0.0, rq = 0.0, m2 = 0.0;
+#pragma clang fp contract(off)
+    double rho = 0.0, rq = 0.0;
 #pragma unroll
     for (int k = 0; k < N; ++k) {
         rho += W[k];
-        rq += W[k] * e.q[k];
+        rq = fma(W[k], e.q[k], rq);
     }
-#pragma unroll
-    for (int d = 0; d < D; ++d) m2 += W[N + d] * W[N + d];
-    return W[N + D] - 0.5 * m2 / rho - rq;
+    return W[N + D] - 0.5 * sum_of_squares<D>(W + N) / rho - rq;
 }
 
 // num/den for a den as rcp_newton takes it: the hardware reciprocal's
@@ -399,11 +410,12 @@ __device__ inline void weno_is_pair(const float* v, double eps, float& l, float&
 template <typename R>
 __device__ inline R hllc_speeds(R uL, R uR, R pL, R pR, R rhoL, R rhoR, R cL, R cR, R& sL, R& sR)
 {
+#pragma clang fp contract(off)
     const R ub = (R)0.5 * (uL + uR), cb = (R)0.5 * (cL + cR);
     sL = fmin(ub - cb, uL - cL);
     sR = fmax(ub + cb, uR + cR);
     const R dL = sL - uL, dR = sR - uR;
-    return div_rn(pR - pL + rhoL * uL * dL - rhoR * uR * dR, rhoL * dL - rhoR * dR);
+    return div_rn(fma(-(rhoR * uR), dR, fma(rhoL * uL, dL, pR - pL)), fma(rhoL, dL, -(rhoR * dR)));
 }
 
 // Sec. 4.1.1 HLLC for the five-equation model in direction DIR.  Writes
@@ -419,6 +431,7 @@ __device__ inline R hllc_speeds(R uL, R uR, R pL, R pR, R rhoL, R rhoR, R cL, R 
 template <int N, int D, int DIR>
 __device__ inline double hllc(const St<N, D>& L, const St<N, D>& Rs, double* G)
 {
+#pragma clang fp contract(off)
     constexpr int IE = N + D, IA = N + D + 1;
     double sL, sR;
     const double ss =
@@ -452,6 +465,7 @@ __device__ inline double hllc(const St<N, D>& L, const St<N, D>& Rs, double* G)
 template <int N, int D, int DIR>
 __device__ inline float hllc(const St<N, D, float>& L, const St<N, D, float>& Rs, double* G)
 {
+#pragma clang fp contract(off)
     using R = float;
     constexpr int IE = N + D, IA = N + D + 1;
     R sL, sR;
@@ -462,24 +476,35 @@ __device__ inline float hllc(const St<N, D, float>& L, const St<N, D, float>& Rs
     const R wl = (R)0.5 * ((R)1 + sg), wr = (R)0.5 * ((R)1 - sg);
     const R sm = fmin((R)0, sL), sp = fmax((R)0, sR);
     const R qL = div_rn(ss - uL, sL - ss), qR = div_rn(ss - uR, sR - ss);
+    auto mix = [&](R l, R r) {
+#pragma clang fp contract(off)
+        return fma(wl, l, wr * r);
+    };
 #pragma unroll
     for (int k = 0; k < N; ++k)
-        G[k] = wl * (L.ar[k] * uL + sm * (qL * L.ar[k])) + wr * (Rs.ar[k] * uR + sp * (qR * Rs.ar[k]));
+        G[k] = mix(fma(L.ar[k], uL, sm * (qL * L.ar[k])), fma(Rs.ar[k], uR, sp * (qR * Rs.ar[k])));
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-        const R FLd = L.mom[d] * uL + (d == DIR ? L.p : (R)0);
-        const R FRd = Rs.mom[d] * uR + (d == DIR ? Rs.p : (R)0);
+        const R FLd = d == DIR ? fma(L.mom[d], uL, L.p) : L.mom[d] * uL;
+        const R FRd = d == DIR ? fma(Rs.mom[d], uR, Rs.p) : Rs.mom[d] * uR;
         const R JL = d == DIR ? L.rho * sL * qL : qL * L.mom[d];
         const R JR = d == DIR ? Rs.rho * sR * qR : qR * Rs.mom[d];
-        G[N + d] = wl * (FLd + sm * JL) + wr * (FRd + sp * JR);
+        G[N + d] = mix(fma(sm, JL, FLd), fma(sp, JR, FRd));
     }
-    const R JL = qL * (L.E + L.p + L.rho * ss * dL);
-    const R JR = qR * (Rs.E + Rs.p + Rs.rho * ss * dR);
-    G[IE] = wl * ((L.E + L.p) * uL + sm * JL) + wr * ((Rs.E + Rs.p) * uR + sp * JR);
+    const R JL = qL * fma(L.rho * ss, dL, L.E + L.p);
+    const R JR = qR * fma(Rs.rho * ss, dR, Rs.E + Rs.p);
+    G[IE] = mix(fma(L.E + L.p, uL, sm * JL), fma(Rs.E + Rs.p, uR, sp * JR));
 #pragma unroll
     for (int k = 0; k < N - 1; ++k)
-        G[IA + k] = (double)wl * (L.al[k] * (double)ss) + (double)wr * (Rs.al[k] * (double)ss);
+        G[IA + k] = fma((double)wl, L.al[k] * (double)ss, (double)wr * (Rs.al[k] * (double)ss));
     return ss;
+}
+
+// (1 - t) a + t b in one written order, for values that become a float face's
+__device__ inline double blend(double t, double a, double b)
+{
+#pragma clang fp contract(off)
+    return fma(t, b, (1.0 - t) * a);
 }
 
 // theta solving (1-theta) a + theta b = min(eps, a) when b < min(eps, a); else 1
@@ -489,8 +514,9 @@ __device__ inline double lim_theta(double a, double b, double eps)
     return b < m ? (a - m) / (a - b) : 1.0;
 }
 
-// rho c^2 of a node read back from its record, as state_from_W forms it (the
-// record does not hold it: only the limiter's rare path asks for it)
+// rho c^2 of a node read back from its record (which does not hold it: only the
+// limiter's rare path asks for it, as a bound of about 1e-9), to an ulp as
+// state_from_W forms it
 template <int N, int D>
 __device__ inline void set_rc2(KArg ke, St<N, D>& s)
 {
@@ -507,12 +533,12 @@ __device__ inline void set_rc2(KArg ke, St<N, D>& s)
 // eps^HS, and everything finite (an infinite or NaN slot leaves a bound unmet
 // or makes E or rho c^2 infinite or NaN).  Most faces pass; the nodes are
 // read from LDS and the limiter runs only where one does not.
-template <int N, int D, typename R>
+template <int N, int D, int DIR, typename R>
 __device__ inline bool interp_clean(KArg ke, KArg kp, St<N, D, R>& V)
 {
     const EosDev e = kload<EosDev>(ke);
     const ParDev P = kload<ParDev>(kp);
-    complete_from_prim<N, D, R>(e, V);
+    complete_from_prim<N, D, R, DIR>(e, V);
     bool ok = P.fast_interp_limiter != 0;
 #pragma unroll
     for (int k = 0; k < N; ++k) ok = ok & ((double)V.ar[k] >= P.eps_i_ar) & (V.al[k] >= P.eps_i_a);
@@ -523,7 +549,7 @@ __device__ inline bool interp_clean(KArg ke, KArg kp, St<N, D, R>& V)
 // (partial densities and volume fractions are blended toward the node state;
 // velocity and pressure are kept), then the hard switch to the node state.
 // On return V is a complete state (conservative slots, rho, c, rho c^2).
-template <int N, int D, typename R>
+template <int N, int D, int DIR, typename R>
 __device__ inline void interp_limit(KArg ke, KArg kp, St<N, D, R>& V, const St<N, D, R>& node, unsigned& cnt)
 {
     const EosDev e = kload<EosDev>(ke);
@@ -534,7 +560,7 @@ __device__ inline void interp_limit(KArg ke, KArg kp, St<N, D, R>& V, const St<N
         const double m = fmin(P.eps_i_ar, a);
         if (b < m) {
             const double th = (a - m) / (a - b);
-            V.ar[k] = (R)((1.0 - th) * a + th * b);
+            V.ar[k] = (R)blend(th, a, b);
             cnt += cnt_one(C_ALG1);
         }
     }
@@ -550,11 +576,11 @@ __device__ inline void interp_limit(KArg ke, KArg kp, St<N, D, R>& V, const St<N
     for (int k = 0; k < N; ++k) th = fmin(th, lim_theta((double)node.al[k], at[k], P.eps_i_a));
     if (th < 1.0) {
 #pragma unroll
-        for (int k = 0; k < N - 1; ++k) V.al[k] = (1.0 - th) * node.al[k] + th * V.al[k];
+        for (int k = 0; k < N - 1; ++k) V.al[k] = blend(th, node.al[k], V.al[k]);
         cnt += cnt_one(C_ALG2);
     }
     // hard switch, judged on the completed limited state
-    complete_from_prim<N, D, R>(e, V);
+    complete_from_prim<N, D, R, DIR>(e, V);
     bool hs = !isfinite(V.rc2) || !isfinite(V.p);
 #pragma unroll
     for (int k = 0; k < N; ++k) {
@@ -654,11 +680,19 @@ __device__ inline bool flux_limit_clean(KArg ke, KArg kp, const St<N, D>& L, con
     return ok & (tp >= 0.0) & (tm >= 0.0) & isfinite(tp) & isfinite(tm);
 }
 
-template <int N, int D, int DIR>
+//
+// Every product of the half-cell states is rounded or fused as written here,
+// so that all kernels limit a face to the same bits.  FUSED (float faces): the
+// high-order states take u W in one rounding with the flux it is subtracted
+// from, as the check above does; another last bit of theta there is now and
+// then another float in the cells beside the face (1e-5 of their momentum
+// after ten steps of a three-species tube).
+template <int N, int D, int DIR, bool FUSED>
 __device__ inline void flux_limit(KArg ke, KArg kp, const St<N, D>& L, const St<N, D>& R, double lam,
                                   const double* Gho, const double* Gho_p, const double* Glo, const double* Glo_p,
                                   double* G, double* Gp, unsigned& cnt)
 {
+#pragma clang fp contract(off)
     constexpr int M = 2 * N + D, IE = N + D, IA = N + D + 1;
     const EosDev e = kload<EosDev>(ke);
     const ParDev P = kload<ParDev>(kp);
@@ -675,8 +709,8 @@ __device__ inline void flux_limit(KArg ke, KArg kp, const St<N, D>& L, const St<
     for (int d = 0; d < D; ++d) {
         WL[N + d] = L.mom[d];
         WR[N + d] = R.mom[d];
-        FL[N + d] = L.mom[d] * uL + (d == DIR ? L.p : 0.0);
-        FR[N + d] = R.mom[d] * uR + (d == DIR ? R.p : 0.0);
+        FL[N + d] = d == DIR ? fma(L.mom[d], uL, L.p) : L.mom[d] * uL;
+        FR[N + d] = d == DIR ? fma(R.mom[d], uR, R.p) : R.mom[d] * uR;
     }
     WL[IE] = L.E;
     WR[IE] = R.E;
@@ -695,8 +729,8 @@ __device__ inline void flux_limit(KArg ke, KArg kp, const St<N, D>& L, const St<
 #pragma unroll
     for (int c = 0; c < M; ++c) {
         const double gp = c >= IA ? Glo_p[c - IA] : Glo[c];
-        Wp_lo[c] = WL[c] - l2 * (Glo[c] - FL[c]);
-        Wm_lo[c] = WR[c] + l2 * (gp - FR[c]);
+        Wp_lo[c] = fma(-l2, Glo[c] - FL[c], WL[c]);
+        Wm_lo[c] = fma(l2, gp - FR[c], WR[c]);
     }
     double ap_lo[N], am_lo[N];
     alphas<N, D>(Wp_lo, ap_lo);
@@ -708,8 +742,14 @@ __device__ inline void flux_limit(KArg ke, KArg kp, const St<N, D>& L, const St<
 #pragma unroll
     for (int c = 0; c < M; ++c) {
         const double gp = c >= IA ? Gho_p[c - IA] : Gho[c];
-        Wp[c] = WL[c] - l2 * (Gho[c] - FL[c]);
-        Wm[c] = WR[c] + l2 * (gp - FR[c]);
+        double jp = Gho[c] - FL[c], jm = gp - FR[c];
+        if constexpr (FUSED)
+            if (c < N || c == IE) {
+                jp = fma(-uL, c < N ? L.ar[c < N ? c : 0] : L.E + L.p, Gho[c]);
+                jm = fma(-uR, c < N ? R.ar[c < N ? c : 0] : R.E + R.p, Gho[c]);
+            }
+        Wp[c] = fma(-l2, jp, WL[c]);
+        Wm[c] = fma(l2, jm, WR[c]);
     }
     double th = 1.0;
 #pragma unroll
@@ -750,31 +790,31 @@ __device__ inline void flux_limit(KArg ke, KArg kp, const St<N, D>& L, const St<
     }
     double Gs[M], Gsp[N > 1 ? N - 1 : 1];
 #pragma unroll
-    for (int c = 0; c < M; ++c) Gs[c] = (1.0 - th) * Glo[c] + th * Gho[c];
+    for (int c = 0; c < M; ++c) Gs[c] = blend(th, Glo[c], Gho[c]);
 #pragma unroll
-    for (int k = 0; k < N - 1; ++k) Gsp[k] = (1.0 - th) * Glo_p[k] + th * Gho_p[k];
+    for (int k = 0; k < N - 1; ++k) Gsp[k] = blend(th, Glo_p[k], Gho_p[k]);
 
     // Alg. 4
 #pragma unroll
     for (int c = 0; c < M; ++c) {
         const double gp = c >= IA ? Gsp[c - IA] : Gs[c];
-        Wp[c] = WL[c] - l2 * (Gs[c] - FL[c]);
-        Wm[c] = WR[c] + l2 * (gp - FR[c]);
+        Wp[c] = fma(-l2, Gs[c] - FL[c], WL[c]);
+        Wm[c] = fma(l2, gp - FR[c], WR[c]);
     }
     const double th2 = fmin(lim_theta(rep_lo, rhoe_tilde<N, D>(e, Wp), P.eps_f_re),
                             lim_theta(rem_lo, rhoe_tilde<N, D>(e, Wm), P.eps_f_re));
     if (th2 < 1.0) cnt += cnt_one(C_ALG4);
 #pragma unroll
-    for (int c = 0; c < M; ++c) G[c] = (1.0 - th2) * Glo[c] + th2 * Gs[c];
+    for (int c = 0; c < M; ++c) G[c] = blend(th2, Glo[c], Gs[c]);
 #pragma unroll
-    for (int k = 0; k < N - 1; ++k) Gp[k] = (1.0 - th2) * Glo_p[k] + th2 * Gsp[k];
+    for (int k = 0; k < N - 1; ++k) Gp[k] = blend(th2, Glo_p[k], Gsp[k]);
 
     // hard switch on the final half-cell states
 #pragma unroll
     for (int c = 0; c < M; ++c) {
         const double gp = c >= IA ? Gp[c - IA] : G[c];
-        Wp[c] = WL[c] - l2 * (G[c] - FL[c]);
-        Wm[c] = WR[c] + l2 * (gp - FR[c]);
+        Wp[c] = fma(-l2, G[c] - FL[c], WL[c]);
+        Wm[c] = fma(l2, gp - FR[c], WR[c]);
     }
     bool hs = false;
 #pragma unroll

@@ -109,6 +109,37 @@ __device__ inline double sensor_product(const double* r, const double* p)
            (sensor_ratio(n[2], d[2]) + sensor_ratio(n[3], d[3]));
 }
 
+// The same product for float faces, ratio by ratio.  The blending weight that
+// comes of it is rounded to float and multiplies fluxes of the size of a
+// liquid's pressure, so another last bit here is now and then another float
+// there: 1e-5 of the momentum of single cells (three species, ten steps).
+// Hence one written order, whose products are fused as written.
+__device__ inline double sensor_ratio_float(double v0, double v1, double v2, double v3, double v4)
+{
+    const double num = fabs(fma(16.0, v3, fma(-30.0, v2, fma(16.0, v1, -v0))) - v4);
+    const double den = fabs(fma(16.0, v3, fma(30.0, v2, fma(16.0, v1, v0))) + v4);
+    return den > 1e-290 ? num * rcp_newton(den) : sensor_ratio(num, den);
+}
+__device__ inline double sensor_product_float(const double* r, const double* p)
+{
+#pragma clang fp contract(off)
+    const double sr = 0.5 * (sensor_ratio_float(r[1], r[2], r[3], r[4], r[5]) +
+                             sensor_ratio_float(r[0], r[1], r[2], r[3], r[4]));
+    const double sp = 0.5 * (sensor_ratio_float(p[1], p[2], p[3], p[4], p[5]) +
+                             sensor_ratio_float(p[0], p[1], p[2], p[3], p[4]));
+    return sr * sp;
+}
+
+// HCS reconstruction (eq:reconstructed_G) of a double slot of the float faces
+// from its midpoint value t and the sums of the node pairs (i, i+1), (i-1, i+2)
+// and (i-2, i+3), blended with t by sig; one written order, as above
+__device__ inline double hcs_blend(const ParDev& P, double sig, double t, double g23, double g14, double g05)
+{
+#pragma clang fp contract(off)
+    const double h = fma(-P.hcs_c, g05, fma(P.hcs_b, g14, fma(P.psi, t, -(P.hcs_a * g23))));
+    return fma(sig, t, (1.0 - sig) * h);
+}
+
 // Output: G = G^{**,-}_{i+1/2} (M slots) and Gp = alpha slots of G^{**,+}.
 // ke and kp: the species table and the parameters in the kernel arguments.
 // R is the face arithmetic type; node data, the flux limiter and the outputs
@@ -154,8 +185,9 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
         const double ss = hllc<N, D, DIR>(Lr, Rr, Glo);
 #pragma unroll
         for (int k = 0; k < N - 1; ++k) {
-            Glo_p[k] = Glo[IA + k] - ss * Rr.al[k];
-            Glo[IA + k] = Glo[IA + k] - ss * Lr.al[k];
+#pragma clang fp contract(off)
+            Glo_p[k] = DELTA ? Glo[IA + k] - ss * Rr.al[k] : fma(-ss, Rr.al[k], Glo[IA + k]);
+            Glo[IA + k] = fma(-ss, Lr.al[k], Glo[IA + k]);
         }
     };
     const int flags = kload<ParDev>(kp).flags;
@@ -245,19 +277,19 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
 
     // Sec. 4.3.2 interpolation limiter: left against node i, right against node i+1
     if (!(flags & F_NO_LIMITERS)) {
-        const bool cl = interp_clean<N, D, R>(ke, kp, VL), cr = interp_clean<N, D, R>(ke, kp, VR);
+        const bool cl = interp_clean<N, D, DIR, R>(ke, kp, VL), cr = interp_clean<N, D, DIR, R>(ke, kp, VR);
         if (__builtin_expect(!(cl & cr), 0)) {
             St<N, D> L, Rn;
             node_pair(L, Rn);
             set_rc2<N, D>(ke, L);
             set_rc2<N, D>(ke, Rn);
-            interp_limit<N, D, R>(ke, kp, VL, convert<N, D, R>(L), cnt);  // also completes the state
-            interp_limit<N, D, R>(ke, kp, VR, convert<N, D, R>(Rn), cnt);
+            interp_limit<N, D, DIR, R>(ke, kp, VL, convert<N, D, R>(L), cnt);  // also completes the state
+            interp_limit<N, D, DIR, R>(ke, kp, VR, convert<N, D, R>(Rn), cnt);
         }
     } else {
         const EosDev e = kload<EosDev>(ke);
-        complete_from_prim<N, D, R>(e, VL);
-        complete_from_prim<N, D, R>(e, VR);
+        complete_from_prim<N, D, R, DIR>(e, VL);
+        complete_from_prim<N, D, R, DIR>(e, VR);
     }
 
     // midpoint flux and velocity from HLLC on the interpolated states
@@ -276,7 +308,7 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
             r[j] = nodev<NS, FS>(nd, j, F::RHO);
             pr[j] = nodev<NS, FS>(nd, j, F::P);
         }
-        const double z = sensor_product(r, pr);
+        const double z = DELTA ? sensor_product_float(r, pr) : sensor_product(r, pr);
         const double arg = P.Cs * (P.qexp == 2.0 ? z * z : pow(z, P.qexp));
         // tanh is exactly 0 at 0 and rounds to 1 for arguments >= 22; below
         // 0.01 (smooth flow: nearly every face) its odd series to x^7 is
@@ -324,7 +356,6 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
         }
     } else {
         const R psi = (R)P.psi, ha = (R)P.hcs_a, hb = (R)P.hcs_b, hc = (R)P.hcs_c;
-        const double psid = P.psi, had = P.hcs_a, hbd = P.hcs_b, hcd = P.hcs_c;
         R un[6], pj[6];
         double und[6];
 #pragma unroll
@@ -337,11 +368,11 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
 #pragma unroll
         for (int c = 0; c < M; ++c) {
             if (c >= IA) {
-                double g[6];
-#pragma unroll
-                for (int j = 0; j < 6; ++j) g[j] = nodev<NS, FS>(nd, j, c) * und[j];
-                const double ghcs = psid * Gt[c] - had * (g[2] + g[3]) + hbd * (g[1] + g[4]) - hcd * (g[0] + g[5]);
-                Gho[c] = sigd * Gt[c] + (1.0 - sigd) * ghcs;
+                auto pair = [&](int i, int j) {
+#pragma clang fp contract(off)
+                    return fma(nodev<NS, FS>(nd, i, c), und[i], nodev<NS, FS>(nd, j, c) * und[j]);
+                };
+                Gho[c] = hcs_blend(P, sigd, Gt[c], pair(2, 3), pair(1, 4), pair(0, 5));
             } else {
                 R g[6];
 #pragma unroll
@@ -359,17 +390,14 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
                 Gho[c] = (double)(sig * gt + ((R)1 - sig) * ghcs);
             }
         }
-        const double utd = ut;
-        const double uhcs =
-            psid * utd - had * (und[2] + und[3]) + hbd * (und[1] + und[4]) - hcd * (und[0] + und[5]);
-        uh = sigd * utd + (1.0 - sigd) * uhcs;
+        uh = hcs_blend(P, sigd, (double)ut, und[2] + und[3], und[1] + und[4], und[0] + und[5]);
     }
 
     // high-order quasi-conservative pair: alpha slots minus u-hat alpha_i / alpha_{i+1}
 #pragma unroll
     for (int k = 0; k < N - 1; ++k) {
-        Gho_p[k] = Gho[IA + k] - uh * nodev<NS, FS>(nd, 3, IA + k);
-        Gho[IA + k] = Gho[IA + k] - uh * nodev<NS, FS>(nd, 2, IA + k);
+        Gho_p[k] = fma(-uh, nodev<NS, FS>(nd, 3, IA + k), Gho[IA + k]);
+        Gho[IA + k] = fma(-uh, nodev<NS, FS>(nd, 2, IA + k), Gho[IA + k]);
     }
     if (flags & F_NO_LIMITERS) {
 #pragma unroll
@@ -399,7 +427,7 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
     if constexpr (sizeof(R) == sizeof(double)) node_pair(Lf, Rf);
     double Glo[M], Glo_p[NA];
     first_order(Lf, Rf, Glo, Glo_p);
-    flux_limit<N, D, DIR>(ke, kp, Lf, Rf, lam, Gho, Gho_p, Glo, Glo_p, G, Gp, cnt);
+    flux_limit<N, D, DIR, DELTA>(ke, kp, Lf, Rf, lam, Gho, Gho_p, Glo, Glo_p, G, Gp, cnt);
 }
 
 }  // namespace hrm
