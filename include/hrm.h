@@ -343,7 +343,10 @@ int hrm_reset_diagnostics(hrm_ctx* ctx, void* stream);
  * around each launch of the selected kinds (bit k of `mask` selects kind k).
  * For measurement only: event records add a few microseconds per launch.
  * When more than 4096 launches are pending the recording call synchronises
- * its stream to fold them into the totals. */
+ * its stream to fold them into the totals.  With any timer on, lines and small
+ * planes run the sweeps one by one instead of the kernels that take a step or
+ * both directions in one launch, which no timer covers: up to twice as slow, the
+ * same results to the bit. */
 #define HRM_T_SWEEP_X 0    /* k_sweep, direction 0 */
 #define HRM_T_SWEEP_Y 1    /* k_sweep, direction 1 */
 #define HRM_T_SWEEP_Z 2    /* k_sweep, direction 2 */

@@ -19,7 +19,8 @@
 //                     hrm_max_wavespeed), then k_reduce_max / k_reduce_dt
 //                     (which clears the slots the sweep folds into).
 //   k_dt              the time step and lambda_d on the device.
-// Lines of up to LINE_CELLS cells advance in one workgroup (hrm_line.hip).
+// Lines take other kernels (hrm_line.hip): short ones all steps in one workgroup,
+// longer ones a launch per step (line_cells, line_fits).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -407,19 +408,20 @@ __global__ void __launch_bounds__(BS* BA, (sweep_waves<D, DIR, R, WT>())) k_swee
         const int bl = PK ? ts : base(ta, ts), br = PK ? ts + 1 : base(ta, ts + 1);
         double L[M];
 #pragma unroll
-        for (int c = 0; c < IA; ++c) L[c] = -(lds[c * FS + br] - lds[c * FS + bl]) * A.idx;
+        for (int c = 0; c < IA; ++c) L[c] = flux_difference(lds[c * FS + br], lds[c * FS + bl], A.idx);
 #pragma unroll
-        for (int k = 0; k < N - 1; ++k) L[IA + k] = -(lds[(IA + k) * FS + br] - lds[(M + k) * FS + bl]) * A.idx;
+        for (int k = 0; k < N - 1; ++k)
+            L[IA + k] = flux_difference(lds[(IA + k) * FS + br], lds[(M + k) * FS + bl], A.idx);
         if (A.mode == MODE_WRITE) {
 #pragma unroll
             for (int c = 0; c < M; ++c) A.rhs[c * nc + cell] = L[c];
         } else if (A.mode == MODE_ADD) {
             if constexpr (MID) {
 #pragma unroll
-                for (int c = 0; c < M; ++c) A.rhs[c * nc + cell] = Rc[c] + L[c];
+                for (int c = 0; c < M; ++c) A.rhs[c * nc + cell] = add_direction(Rc[c], L[c]);
             } else {
 #pragma unroll
-                for (int c = 0; c < M; ++c) A.rhs[c * nc + cell] += L[c];
+                for (int c = 0; c < M; ++c) A.rhs[c * nc + cell] = add_direction(A.rhs[c * nc + cell], L[c]);
             }
         } else {
             const double dt = D == 1 ? dt_step : A.slot[0];
@@ -432,8 +434,8 @@ __global__ void __launch_bounds__(BS* BA, (sweep_waves<D, DIR, R, WT>())) k_swee
             } else {
 #pragma unroll
                 for (int c = 0; c < M; ++c) {
-                    const double Lc = D > 1 ? A.rhs[c * nc + cell] + L[c] : L[c];
-                    w[c] = A.a * A.Wn[c * nc + cell] + A.b * (A.Ws[c * nc + cell] + dt * Lc);
+                    const double Lc = D > 1 ? add_direction(A.rhs[c * nc + cell], L[c]) : L[c];
+                    w[c] = stage_value(A.a, A.b, A.Wn[c * nc + cell], A.Ws[c * nc + cell], dt, Lc);
                 }
                 if (A.relax && !relax_cell<N, D>(kload<EosDev>(kernel_args() + offsetof(SweepArgs, e)), w))
                     cnt += cnt_one(C_RELAX_BAD);
@@ -591,9 +593,9 @@ __global__ void __launch_bounds__(256, 2) k_plane(const PlaneArgs A)
 #pragma unroll
             for (int c = 0; c < M; ++c) {
                 const int m = c >= IA ? M + c - IA : c;  // the pair's slots of the volume fractions
-                const double Lx = -(lds[c * FS + bx + 1] - lds[m * FS + bx]) * A.s.idx;
-                const double Ly = -(lds[c * FS + by + PLANE_X] - lds[m * FS + by]) * A.idx;
-                w[c] = A.s.a * A.s.Wn[c * nc + cell] + A.s.b * (A.s.Ws[c * nc + cell] + dt * (Lx + Ly));
+                const double Lx = flux_difference(lds[c * FS + bx + 1], lds[m * FS + bx], A.s.idx);
+                const double Ly = flux_difference(lds[c * FS + by + PLANE_X], lds[m * FS + by], A.idx);
+                w[c] = stage_value(A.s.a, A.s.b, A.s.Wn[c * nc + cell], A.s.Ws[c * nc + cell], dt, add_direction(Lx, Ly));
             }
             if (A.s.relax && !relax_cell<N, D>(kload<EosDev>(kernel_args() + offsetof(SweepArgs, e)), w)) cnt += cnt_one(C_RELAX_BAD);
         }

@@ -193,8 +193,8 @@ __global__ void __launch_bounds__(BS, 3) k_batch(const BatchArgs A)
 #pragma unroll
                         for (int c = 0; c < M; ++c) {
                             const double gp = c >= IA ? lds[(M + c - IA) * FS + ts] : lds[c * FS + ts];
-                            const double L = -(lds[c * FS + ts + 1] - gp) * idx;
-                            w[c] = ca * A.W[c * T + cell] + cb * (Ws[c * T + cell] + dt * L);
+                            const double L = flux_difference(lds[c * FS + ts + 1], gp, idx);
+                            w[c] = stage_value(ca, cb, A.W[c * T + cell], Ws[c * T + cell], dt, L);
                         }
                         if (!relax_cell<N, D>(kload<EosDev>(ka + offsetof(BatchArgs, e)), w)) cnt += cnt_one(C_RELAX_BAD);
 #pragma unroll

@@ -1022,6 +1022,25 @@ __device__ inline void hrm4_pc(const EosDev& e, const St<N, D>& s, double& p, do
         p = c = __builtin_nan("");
 }
 
+// A cell's slot of -(G_{i+1/2} - G_{i-1/2}) / dx, the sum of two directions' and
+// its Shu-Osher stage a W^n + b (W^s + dt L): one written order in every kernel
+// that takes a step.  (An addition that may be contracted takes a product from a
+// function that may not: the sum needs its own.)
+__device__ inline double flux_difference(double gr, double gl, double idx)
+{
+#pragma clang fp contract(off)
+    return -(gr - gl) * idx;
+}
+__device__ inline double add_direction(double L, double next)
+{
+#pragma clang fp contract(off)
+    return L + next;
+}
+__device__ inline double stage_value(double a, double b, double wn, double ws, double dt, double L)
+{
+    return fma(a, wn, b * fma(dt, L, ws));
+}
+
 struct DtArgs {
     int D;
     double dx[3];

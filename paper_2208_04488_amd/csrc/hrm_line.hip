@@ -1,14 +1,16 @@
 // hrm_line.hip -- SSP-RK3 steps of one line (1D grid) with all stages in one
 // launch (gfx950): the smallest grids, whose steps are launch and latency bound.
 //
-// k_line: all steps of a short line in one workgroup.  A thread owns a cell, whose state stays in registers from the first step to
-// the last, and the face on its low side.  The node records of a stage and the
+// k_line: all steps of a short line in one workgroup.  A thread owns a cell, whose
+// state stays in registers from the first step to the last, and the face on its
+// low side.  The node records of a stage and the
 // face fluxes are exchanged through LDS, the time step by a reduction over the
 // workgroup, so a step needs neither memory nor another launch: two species,
 // high order, a step of 256 / 400 cells 21.6 / 20.7 us against 35 as four launches
 // (a reduction and three sweeps); four equations, 400 cells 9.9 against 25 us.
 // k_line_step: a longer line in tiles, a launch per step.  The arithmetic is
-// k_sweep's, in the same order, and so are the bits.
+// k_sweep's, in the order that the shared functions write out (hrm_device.hpp),
+// and so are the bits.
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
@@ -113,8 +115,7 @@ __device__ __forceinline__ void line_update(double* lds, int ts, int n, int stag
 #pragma unroll
             for (int c = 0; c < M; ++c) {
                 const double gm = c >= IA ? lds[(M + c - IA) * FS + ts] : lds[c * FS + ts];
-                const double L = -(lds[c * FS + ts + 1] - gm) * idx;
-                w[c] = ca * Wn[c] + cb * (w[c] + dt * L);
+                w[c] = stage_value(ca, cb, Wn[c], w[c], dt, flux_difference(lds[c * FS + ts + 1], gm, idx));
             }
             if (!relax_cell<N, D>(kload<EosDev>(kernel_args() + offsetof(LineArgs, e)), w) && count_cell)
                 cnt += cnt_one(C_RELAX_BAD);
