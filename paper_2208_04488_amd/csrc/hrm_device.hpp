@@ -987,24 +987,25 @@ __device__ inline bool relax_cell(const EosDev& e, double* W)
 // S_v p - C'/p.  So
 //   c^2 = p (re + p) (S_R p + pinf_1 S_2) / (rho (S_v p^2 + re pinf_1 S_2)),
 // a quotient of positive terms (no cancellation, unlike 2 A_p p + B_p).
-// p = c = NaN outside the admissible set.
+// p = c = NaN outside the admissible set.  Written out as state_from_W is: the
+// time step is taken from this c, in the pass before the first step and in the
+// kernels that take one, and has to be the same.
 template <int N, int D>
 __device__ inline double hrm4_c(const EosDev& e, const St<N, D>& s, double p)
 {
-    double rho = 0.0, Sv = 0.0, SR = 0.0, rq = 0.0, m2 = 0.0;
+#pragma clang fp contract(off)
+    double rho = 0.0, Sv = 0.0, SR = 0.0, rq = 0.0;
 #pragma unroll
     for (int k = 0; k < N; ++k) {
         rho += s.ar[k];
-        Sv += s.ar[k] * e.cv[k];
-        SR += s.ar[k] * (e.cp[k] - e.cv[k]);
-        rq += s.ar[k] * e.q[k];
+        Sv = fma(s.ar[k], e.cv[k], Sv);
+        SR = fma(s.ar[k], e.cp[k] - e.cv[k], SR);
+        rq = fma(s.ar[k], e.q[k], rq);
     }
-#pragma unroll
-    for (int d = 0; d < D; ++d) m2 += s.mom[d] * s.mom[d];
-    const double re = s.E - div_rn(0.5 * m2, rho) - rq;
-    const double S2 = SR - s.ar[0] * (e.cp[0] - e.cv[0]);
+    const double re = s.E - div_rn(0.5 * sum_of_squares<D>(s.mom), rho) - rq;
+    const double S2 = fma(-s.ar[0], e.cp[0] - e.cv[0], SR);
     const double p1 = e.pinf[0];
-    return sqrt_rn(div_rn(p * (re + p) * (SR * p + p1 * S2), rho * (Sv * p * p + re * p1 * S2)));
+    return sqrt_rn(div_rn(p * (re + p) * fma(p1, S2, SR * p), rho * fma(re * p1, S2, Sv * p * p)));
 }
 
 template <int N, int D>

@@ -75,3 +75,68 @@ def test_planes(H, n, kind):
     if kind == "inflow":
         prob.boundary = {(0, 0): np.ascontiguousarray(W[:, :, :, 0]), (1, 1): np.ascontiguousarray(W[:, :, -1, :])}
     _same(H, prob, 5, precision=H.FP32 if kind.endswith("fp32") else H.FP64)
+
+
+def _line(kind, n):
+    if kind == "three":
+        return I.shock_interface(n)
+    if kind == "four_eq":
+        return I.shock_tube(n)
+    return I.config1(n)
+
+
+# lines beyond one workgroup, whose maximum wavespeed comes from a pass of its own
+# before the first step and from the step before in every other; learned weights
+# and the timers take the sweeps, the first of which forms the time step
+@pytest.mark.parametrize("steps", [4, 5])
+@pytest.mark.parametrize("kind", ["plain", "three", "fp32", "dirichlet", "first", "four_eq", "four_eq_dirichlet",
+                                  "learned", "learned_dirichlet", "timers_dirichlet", "timers_four_eq"])
+def test_steps_of_a_long_line(H, kind, steps):
+    """hrm_advance(K) against K calls of hrm_step."""
+    import torch
+    from paper_2208_04488_amd import learned
+    base = _line("four_eq" if "four_eq" in kind else kind, 1003)
+    bc = (I.DIRICHLET, I.TRANSMISSIVE) if kind.endswith("dirichlet") else (0, 0)
+    prob = I.Problem(base.name, base.eos, 1, base.n, base.dx, [bc], base.W, cfl=0.4)
+    if kind.endswith("dirichlet"):
+        # faster than any cell: the ghost state sets the time step
+        ghost = base.W[:, 0, 0, :1].copy()
+        ghost[base.eos.N] += 3000.0 * ghost[:base.eos.N].sum()
+        ghost[base.eos.N + 1] += 0.5 * 3000.0 ** 2 * ghost[:base.eos.N].sum()
+        prob.boundary = {(0, 0): np.ascontiguousarray(ghost)}
+    flags = H.FUSE_RELAX | (H.FIRST_ORDER if kind == "first" else H.FOUR_EQ if "four_eq" in kind else 0)
+    p = learned.init_params(5, last_scale=0.3) if kind.startswith("learned") else None
+    runs = []
+    for whole in (True, False):
+        s = H.Solver(prob, flags=flags, precision=H.FP32 if kind == "fp32" else H.FP64, mlp=p)
+        if kind.startswith("timers"):
+            H.hrm_set_timing(s.ctx, 1)
+        for _ in range(1 if whole else steps):
+            s.advance(steps, cfl=0.4) if whole else s.step(cfl=0.4)
+        torch.cuda.synchronize()
+        runs.append((s.W.clone(), s.slot.clone(), s.diagnostics()))
+        s.close()
+    (a, sa, da), (b, sb, db) = runs
+    assert torch.isfinite(a).all() and float(sa[0]) > 0.0
+    assert torch.equal(a, b) and torch.equal(sa, sb) and da == db
+
+
+@pytest.mark.parametrize("species", [2, 3])
+@pytest.mark.parametrize("D", [1, 2, 3])
+def test_sound_speed_of_the_relaxed_model(H, species, D):
+    """The four-equation model's c of hrm_equilibrium_state and of the wavespeed pass, one cell at rest at a time."""
+    import torch
+    eos = I.eos_of(I.LIQ_B, I.AIR, I.HELIUM) if species == 3 else I.eos_of(I.LIQ_A, I.AIR)
+    W = I.random_admissible(eos, D, 64, seed=11, p_range=(1e4, 1e8), u_scale=100.0)
+    M = W.shape[0]
+    mom = W[species:species + D]
+    W[species + D] -= 0.5 * (mom ** 2).sum(axis=0) / W[:species].sum(axis=0)
+    mom[...] = 0.0
+    one = np.ascontiguousarray(W[:, :1].reshape((M, 1, 1, 1)))
+    prob = I.Problem("cell", eos, D, (1,) * D, (1.0,) * D, [(0, 0)] * D, one)
+    s = H.Solver(prob, flags=H.FUSE_RELAX | H.FOUR_EQ)
+    for i in range(W.shape[1]):
+        s.set_state(np.ascontiguousarray(W[:, i].reshape((M, 1, 1, 1))))
+        c = s.equilibrium()[2].ravel()[0]
+        assert np.isfinite(c) and (s.wavespeed() == c).all(), i
+    s.close()
