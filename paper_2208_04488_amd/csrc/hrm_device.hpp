@@ -137,12 +137,14 @@ __device__ inline double rcp_newton(double x)
 }
 
 // a/b and sqrt(x) to the bit of the IEEE operations where operands and results
-// are normal numbers (and 0 numerators): the reciprocal (root) is refined by
-// one step, to about 1e-15, and the exact remainder of the quotient (root) it
-// gives corrects the result to 1e-30 before the last rounding.  6 and 8
+// are normal numbers (and 0 numerators): the reciprocal is refined by one Newton
+// step, the root by one of Goldschmidt's coupled iteration, to about 1e-15, and
+// the remainder of the quotient (root) that gives, formed with a multiply-add
+// (Markstein), corrects the result to 1e-30 before the last rounding.  6 and 11
 // instructions instead of the 11 and 18 of the IEEE sequences, whose operand
 // scaling for subnormal and huge numbers no state needs.  A zero, infinite or
-// NaN divisor and a zero, infinite or negative radicand give NaN or infinity.
+// NaN divisor gives NaN or infinity; 0 and infinity are their own roots, and a
+// negative or NaN radicand gives NaN.  root_rn is the root of a positive number.
 __device__ inline double div_rn(double a, double b)
 {
     const double r0 = __builtin_amdgcn_rcp(b);
@@ -150,7 +152,7 @@ __device__ inline double div_rn(double a, double b)
     const double q = a * r;
     return fma(fma(-b, q, a), r, q);
 }
-__device__ inline double sqrt_rn(double x)
+__device__ inline double root_rn(double x)
 {
     const double r = __builtin_amdgcn_rsq(x);
     double g = x * r, h = 0.5 * r;
@@ -158,6 +160,11 @@ __device__ inline double sqrt_rn(double x)
     g = fma(g, e, g);
     h = fma(h, e, h);
     return fma(fma(-g, g, x), h, g);
+}
+__device__ inline double sqrt_rn(double x)
+{
+    const double r = root_rn(x);
+    return __builtin_amdgcn_class(x, 0x260) ? x : r;  // +-0 and +infinity
 }
 // the quotient in float: the remainder of one that is good to an ulp, times a
 // reciprocal rounded once, is off by 3e-15 before the last rounding
@@ -225,11 +232,12 @@ __device__ inline void state_from_W(const EosDev& e, const double* W, St<N, D>& 
     s.rc2 = fma(fma(re - Pi, iG, Pi), iG, s.p);
     s.rho = rho;
     const double c2 = s.rc2 * irho;
-    s.c = c2 == 0.0 ? 0.0 : sqrt_rn(c2);
+    s.c = c2 == 0.0 ? 0.0 : root_rn(c2);  // a branch: 1 % of the 1000 x 500 step under sqrt_rn's selection
 }
 
-// primitive slots (ar, u, p, al[0..N-2]) already set -> the rest of the state
-template <int N, int D, typename R, int DIR = 0>
+// primitive slots (ar, u, p, al[0..N-2]) already set -> the rest of the state;
+// POSITIVE: c is asked for only where rho c^2 > 0
+template <int N, int D, typename R, int DIR = 0, bool POSITIVE = false>
 __device__ inline void complete_from_prim(const EosDev& e, St<N, D, R>& s)
 {
 #pragma clang fp contract(off)
@@ -252,7 +260,8 @@ __device__ inline void complete_from_prim(const EosDev& e, St<N, D, R>& s)
     s.rho = rho;
     s.E = fma((R)0.5 * rho, u2, fma(Gam, s.p, Pi)) + rq;
     s.rc2 = s.p + div_rn(s.p + Pi, Gam);
-    s.c = sqrt_rn(div_rn(s.rc2, rho));
+    const R c2 = div_rn(s.rc2, rho);
+    s.c = POSITIVE ? root_rn(c2) : sqrt_rn(c2);
 }
 
 // rho(e - qbar) of a conservative vector
@@ -529,8 +538,8 @@ __device__ inline void set_rc2(KArg ke, St<N, D>& s)
 // Completes an interpolated primitive state V and tells whether the limiter
 // below would leave it as it is, without looking at the node: every partial
 // density and volume fraction at or above eps (then b >= eps >= min(eps, a):
-// no blending, and with eps >= eps^HS no hard switch), rho c^2 at or above
-// eps^HS, and everything finite (an infinite or NaN slot leaves a bound unmet
+// no blending, and with eps >= eps^HS no hard switch), rho c^2 positive and at
+// or above eps^HS, and everything finite (an infinite or NaN slot leaves a bound unmet
 // or makes E or rho c^2 infinite or NaN).  Most faces pass; the nodes are
 // read from LDS and the limiter runs only where one does not.
 template <int N, int D, int DIR, typename R>
@@ -538,8 +547,9 @@ __device__ inline bool interp_clean(KArg ke, KArg kp, St<N, D, R>& V)
 {
     const EosDev e = kload<EosDev>(ke);
     const ParDev P = kload<ParDev>(kp);
-    complete_from_prim<N, D, R, DIR>(e, V);
+    complete_from_prim<N, D, R, DIR, true>(e, V);
     bool ok = P.fast_interp_limiter != 0;
+    ok = ok & (V.rc2 > 0);
 #pragma unroll
     for (int k = 0; k < N; ++k) ok = ok & ((double)V.ar[k] >= P.eps_i_ar) & (V.al[k] >= P.eps_i_a);
     return ok & ((double)V.rc2 >= P.hs_i_rc2) & isfinite(V.rc2) & isfinite(V.E);
