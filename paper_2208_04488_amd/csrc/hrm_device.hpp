@@ -683,9 +683,10 @@ __device__ inline bool flux_limit_clean(KArg ke, KArg kp, const St<N, D>& L, con
         sm += am;
     }
     ok = ok & (1.0 - sp >= P.eps_f_a) & (1.0 - sm >= P.eps_f_a);
-    // rho (e - qbar) >= eps of each half-cell state, times rho (positive by the
-    // bounds above).  An infinite or NaN slot fails its bound or leaves these
-    // two products infinite or NaN.
+    // rho (e - qbar) >= eps of each half-cell state, times rho: only where that is
+    // positive, which a caller's bounds need not say.  An infinite or NaN slot
+    // fails its bound or leaves these two products infinite or NaN.
+    ok = ok & (rp > 0.0) & (rm > 0.0);
     const double tp = (Ep - qp - P.eps_f_re) * rp - 0.5 * m2p, tm = (Em - qm - P.eps_f_re) * rm - 0.5 * m2m;
     return ok & (tp >= 0.0) & (tm >= 0.0) & isfinite(tp) & isfinite(tm);
 }
