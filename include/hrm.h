@@ -321,7 +321,7 @@ int hrm_mlp_adam(float* d_params, const float* d_grad, float* d_m, float* d_v, i
  * `stream` for every step with the same (d_W, d_slot, cfl, dt_fixed,
  * t_end); other arguments re-capture.  The graph holds kernel nodes only.
  * Lines (dim 1) with the App. C weights, or of the first-order schemes, take no
- * graph up to 307200 cells (unless timing is on): all steps in one launch on
+ * graph up to 307200 cells (unless timing is on): up to 256 steps in one launch on
  * `stream` up to a few hundred cells, else one launch to set up and one per step.
  * HRM_EINVAL for NULL pointers, nsteps < 0, or neither cfl nor dt_fixed
  * positive; nsteps == 0 launches nothing. */

@@ -1633,7 +1633,7 @@ int hrm_advance(hrm_ctx* c, double* d_W, int nsteps, double cfl, double dt_fixed
     if (nsteps == 0) return HRM_OK;
     hipStream_t s = (hipStream_t)stream;
     c->last_stream = s;
-    // a line: a step, or all of them where one workgroup holds it, in one launch
+    // a line: one step in a launch, or up to LINE_STEPS where one workgroup holds it
     // (the launch timers want the sweeps one by one)
     if (c->D == 1 && !c->timing_mask && hrm::line_fits(c->n[0], c->par.flags, c->precision, c->weights)) {
         if (const int rb = check_boundary(c)) return rb;

@@ -1,7 +1,7 @@
 // hrm_line.hip -- SSP-RK3 steps of one line (1D grid) with all stages in one
 // launch (gfx950): the smallest grids, whose steps are launch and latency bound.
 //
-// k_line: all steps of a short line in one workgroup.  A thread owns a cell, whose
+// k_line: many steps of a short line in one workgroup.  A thread owns a cell, whose
 // state stays in registers from the first step to the last, and the face on its
 // low side.  The node records of a stage and the
 // face fluxes are exchanged through LDS, the time step by a reduction over the
@@ -353,10 +353,14 @@ void launch_steps(int precision, const LineArgs& L, double* other, double* part,
 
 void line_launch(int N, int precision, const LineArgs& A, hipStream_t s)
 {
-    if (N == 2)
-        launch_n<2>(precision, A, s);
-    else
-        launch_n<3>(precision, A, s);
+    LineArgs part = A;
+    for (int done = 0; done < A.nsteps; done += part.nsteps) {
+        part.nsteps = A.nsteps - done < LINE_STEPS ? A.nsteps - done : LINE_STEPS;
+        if (N == 2)
+            launch_n<2>(precision, part, s);
+        else
+            launch_n<3>(precision, part, s);
+    }
 }
 
 void line_steps(int N, int precision, const LineArgs& A, double* other, double* part, hipStream_t s)

@@ -1,5 +1,4 @@
-// hrm_line.hpp -- launch of the one-workgroup advance of a short line
-// (hrm_line.hip).
+// hrm_line.hpp -- launches of the line kernels (hrm_line.hip).
 #pragma once
 
 #include "hrm.h"
@@ -36,6 +35,12 @@ struct LineArgs {
     EosDev e;
     ParDev P;
 };
+
+// Steps of one launch.  A long run is many launches of a few milliseconds (256
+// steps of 400 cells 5.5 ms), so that other work of the device comes between them
+// and the state is in memory at each end; the state and the time carry over to
+// the bit, and a launch costs 0.1 % of its steps.
+constexpr int LINE_STEPS = 256;
 
 // N = 2 or 3, 1 <= A.n <= line_cells(N, ...)
 void line_launch(int N, int precision, const LineArgs& A, hipStream_t s);

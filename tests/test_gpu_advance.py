@@ -402,3 +402,53 @@ def test_small_plane_against_sweeps(H, n, kind):
         assert a.diagnostics() == b.diagnostics()
     a.close()
     b.close()
+
+
+def _captured_launches(call):
+    """Number of nodes of the graph that a call on a stream captures to."""
+    import ctypes
+    import torch
+    with open("/proc/self/maps") as f:
+        path = next(line.split()[-1] for line in f if "libamdhip64.so" in line)
+    hip = ctypes.CDLL(path)
+    stream = torch.cuda.Stream()
+    graph, count = ctypes.c_void_p(), ctypes.c_size_t()
+    torch.cuda.synchronize()
+    assert hip.hipStreamBeginCapture(ctypes.c_void_p(stream.cuda_stream), 2) == 0  # relaxed
+    with torch.cuda.stream(stream):
+        call()
+    assert hip.hipStreamEndCapture(ctypes.c_void_p(stream.cuda_stream), ctypes.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(count)) == 0
+    assert hip.hipGraphDestroy(graph) == 0
+    return count.value
+
+
+def test_long_run_of_a_short_line_in_bounded_launches(H):
+    """600 steps of a line that one workgroup holds: launches of at most 256
+    steps (counted in a capture), the bits of 600 steps taken singly and of a
+    graph's replays."""
+    import torch
+    prob = I.config1(64)
+    a, b = (H.Solver(prob) for _ in range(2))
+    W0 = a.W.clone()
+    a.advance(600, cfl=0.4)
+    for _ in range(600):
+        b.step(cfl=0.4)
+    torch.cuda.synchronize()
+    assert torch.equal(a.W, b.W) and torch.equal(a.slot, b.slot)
+    assert a.diagnostics() == b.diagnostics()
+    W1, slot = a.W.clone(), a.slot.clone()
+    launches = _captured_launches(lambda: a.advance(600, cfl=0.4))
+    print("600 steps in", launches, "launches")
+    assert launches >= 3
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        a.advance(600, cfl=0.4)
+    for _ in range(3):
+        a.W.copy_(W0)
+        a.slot.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(a.W, W1) and torch.equal(a.slot, slot)
+    a.close()
+    b.close()
