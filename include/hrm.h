@@ -388,7 +388,8 @@ const char* hrm_batch_last_error(const hrm_batch* b);
  * and SSP-RK3 steps per launch.  Without a call: 10 steps, and with more than
  * two problems per CU 256 threads and three workgroups per CU, with fewer a
  * workgroup per problem, up to 512 threads wide where some problem is longer
- * than 255 cells.  The shape changes no bit of the result.  A change drops the
+ * than 255 cells.  threads = blocks = 0 takes that shape (again), with the given
+ * steps per launch.  The shape changes no bit of the result.  A change drops the
  * captured graph. */
 int hrm_batch_configure(hrm_batch* b, int threads, int blocks, int steps_per_launch);
 

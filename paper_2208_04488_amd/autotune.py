@@ -5,9 +5,11 @@ workgroup (one face per thread; a tile holds threads - 1 cells, so small
 workgroups waste fewer faces on short problems but stage more halo nodes),
 the number of workgroups (how many problems are in flight at once) and the
 SSP-RK3 steps per launch (launch overhead against the length of the tail
-in which the last long problems run alone).  ``tune_batch`` times a small
-grid of candidates on a private copy of the ensemble and returns the fastest;
-results are cached in a JSON file keyed by device, species count, ensemble
+in which the last long problems run alone).  The library's default shape,
+asked for with threads = workgroups = 0, mixes wide and narrow workgroups for
+ensembles of few problems, which no other candidate does; it is tried first.
+``tune_batch`` times a small grid of candidates on a private copy of the
+ensemble and returns the fastest; results are cached in a JSON file keyed by device, species count, ensemble
 size and precision.
 """
 from __future__ import annotations
@@ -26,13 +28,14 @@ def _cache_path() -> str:
 
 
 def _key(batch, precision, device_name) -> str:
-    return f"{device_name}|N{batch.N}|P{batch.nprob}|T{batch.ncell}|prec{precision}"
+    return f"{device_name}|N{batch.N}|P{batch.nprob}|T{batch.ncell}|prec{precision}|with default"
 
 
 def candidates(cus: int):
-    """(threads, workgroups, steps per launch): one to three waves per SIMD
-    (the kernel's register budget allows three) for 64, 128 and 256 threads."""
-    out = []
+    """(threads, workgroups, steps per launch): the default shape (0, 0), then
+    one to three waves per SIMD (the kernel's register budget allows three) for
+    64, 128 and 256 threads."""
+    out = [(0, 0, k) for k in (5, 20)]
     for threads in (64, 128, 256):
         per_wave = threads // 64
         for waves_per_simd in (1, 2, 3):
@@ -63,8 +66,9 @@ def time_config(solver, W0, shape, steps: int) -> float:
 
 def tune_batch(batch, precision=hrm.FP64, steps: int = 20, use_cache: bool = True,
                shapes: Optional[list] = None, verbose: bool = False) -> dict:
-    """Fastest (threads, blocks, steps_per_launch) for `batch`; the ensemble's
-    own state is not touched (the candidates run on a private handle and copy)."""
+    """Fastest (threads, blocks, steps_per_launch) for `batch`, as
+    hrm_batch_configure takes them; the ensemble's own state is not touched (the
+    candidates run on a private handle and copy)."""
     import torch
     props = torch.cuda.get_device_properties(0)
     key = _key(batch, precision, props.name)

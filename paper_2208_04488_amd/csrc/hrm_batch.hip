@@ -225,6 +225,7 @@ struct hrm_batch {
     int* d_queue;
     unsigned long long* d_cnt;
     int threads, blocks, narrow, ksteps;
+    int def_threads, def_blocks;  // the default shape; narrow belongs to its 512 threads
     hipStream_t cap_stream;
     hipGraphExec_t gexec;
     double* g_W;
@@ -398,6 +399,8 @@ int hrm_batch_create(const hrm_eos* e, const hrm_params* prm, int nprob, const l
         b->threads = 256;
         b->blocks = 3 * cus;
     }
+    b->def_threads = b->threads;
+    b->def_blocks = b->blocks;
     b->ksteps = 10;
 
     const size_t bytes = sizeof(double) * (size_t)b->M * (size_t)b->T;
@@ -448,8 +451,13 @@ int hrm_batch_destroy(hrm_batch* b)
 int hrm_batch_configure(hrm_batch* b, int threads, int blocks, int steps_per_launch)
 {
     if (!b) return HRM_EINVAL;
-    if ((threads != 64 && threads != 128 && threads != 256) || blocks < 1 || blocks > 65536 || steps_per_launch < 1)
-        return bfail(b, HRM_EINVAL, "hrm_batch_configure: threads in {64,128,256}, blocks >= 1, steps >= 1");
+    if (threads == 0 && blocks == 0) {
+        threads = b->def_threads;
+        blocks = b->def_blocks;
+    } else if ((threads != 64 && threads != 128 && threads != 256) || blocks < 1 || blocks > 65536) {
+        return bfail(b, HRM_EINVAL, "hrm_batch_configure: threads in {64,128,256} and blocks >= 1, or both 0");
+    }
+    if (steps_per_launch < 1) return bfail(b, HRM_EINVAL, "hrm_batch_configure: steps >= 1");
     if (threads != b->threads || blocks != b->blocks || steps_per_launch != b->ksteps) drop_graph(b);
     b->threads = threads;
     b->blocks = blocks;

@@ -259,3 +259,46 @@ def test_default_launch_keeps_the_bits(H, I, nprob, nmin, nmax, species, precisi
     assert np.array_equal(ref[0], got[0], equal_nan=True)
     assert np.array_equal(ref[1], got[1], equal_nan=True)
     assert ref[2] == got[2]
+
+
+@pytest.mark.parametrize("precision", ["FP64", "FP32"])
+def test_default_shape_can_be_asked_for(H, I, precision):
+    """Configured away and back, a handle has the default launch again: the bits
+    of one that was never configured, and its speed to a tenth (no other shape
+    mixes wide and narrow workgroups).  The tuner tries that shape, so what it
+    returns is no slower."""
+    import torch
+    from paper_2208_04488_amd import autotune
+    batch = I.config4(lengths=np.random.default_rng(3).integers(300, 1100, size=200), seed=4107)
+    prec = getattr(H, precision)
+    s, ref = (H.BatchSolver(batch, precision=prec) for _ in range(2))
+    s.configure(64, 37, 4)
+    s.run(4)
+    s.configure(0, 0, 8)
+    s.run(8)
+    s.configure(0, 0, 10)
+    s.W.copy_(torch.from_numpy(batch.W))
+    H.hrm_batch_set_end_times(s.b, np.zeros(batch.nprob))
+    s.run(20)
+    ref.run(20)
+    torch.cuda.synchronize()
+    assert torch.equal(s.W, ref.W)
+    best = []
+    for solver in (s, ref):
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(8)]
+        for i in range(7):
+            e[i].record()
+            solver.run(20)
+        e[7].record()
+        torch.cuda.synchronize()
+        best.append(min(e[i].elapsed_time(e[i + 1]) for i in range(7)))
+    print(f"20 steps: {best[0]:.3f} ms configured back, {best[1]:.3f} ms never configured")
+    assert best[0] <= 1.1 * best[1]
+    for bad in ((0, 5, 10), (64, 0, 10), (0, 0, 0)):
+        with pytest.raises(H.HrmError):
+            s.configure(*bad)
+    s.close()
+    ref.close()
+    got = autotune.tune_batch(batch, precision=prec, use_cache=False)
+    default = [t["ms_per_step"] for t in got["tried"] if t["threads"] == 0]
+    assert default and got["ms_per_step"] <= min(default)
