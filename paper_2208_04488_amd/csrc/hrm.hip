@@ -828,13 +828,12 @@ __global__ void __launch_bounds__(64) k_mlp_infer(const MlpPacked* m, const doub
     if (i < n)
 #pragma unroll
         for (int j = 0; j < 5; ++j) u[j] = U[i * 5 + j];
-    double d[5];
     float x[5], z[3], w[3];
-    mlp_inputs(u, d, x);
+    mlp_inputs(u, x);
     mlp_logits(m, x, z);
     const bool ok = mlp_omega(z, x, w);
     if (i < n) {
-        val[i] = ok ? mlp_value(u[2], d, w) : weno_is(u[0], u[1], u[2], u[3], u[4], eps);
+        val[i] = ok ? mlp_value(u, w) : weno_is(u[0], u[1], u[2], u[3], u[4], eps);
 #pragma unroll
         for (int k = 0; k < 3; ++k) om[i * 3 + k] = w[k];
     }

@@ -468,44 +468,70 @@ __device__ inline double hllc(const St<N, D>& L, const St<N, D>& Rs, double* G)
     return ss;
 }
 
-// float: both sides, averaged at s* = 0 (sign(0) = 0).  chi_K U_K - U_K would
-// round to 0 and drop the star-state correction of the flux where |s_K| (a
-// liquid's sound speed) dwarfs |s* - u_K|, hence the closed form here too.
-template <int N, int D, int DIR>
-__device__ inline float hllc(const St<N, D, float>& L, const St<N, D, float>& Rs, double* G)
+// The same solver for the faces that keep their order of rounding: the side the
+// flux is taken from, or at s* = 0 the mean of both (sign(0) = 0; a flow that is
+// symmetric about the face stays so).  In double the jumps are those of the star
+// states U*_K = chi_K (...).  In float they are taken in closed form as above:
+// chi_K U_K - U_K would round to 0 and drop the star-state correction of the flux
+// where |s_K| (a liquid's sound speed) dwarfs |s* - u_K|.  NODES: of two nodes in
+// double, where the products u W are rounded.
+template <int N, int D, int DIR, typename R, bool NODES = false>
+__device__ inline R hllc_kept(const St<N, D, R>& L, const St<N, D, R>& Rs, double* G)
 {
 #pragma clang fp contract(off)
-    using R = float;
-    constexpr int IE = N + D, IA = N + D + 1;
+    constexpr int M = 2 * N + D, IE = N + D, IA = N + D + 1;
+    constexpr bool CHI = sizeof(R) == sizeof(double);
     R sL, sR;
     const R uL = L.u[DIR], uR = Rs.u[DIR];
     const R ss = hllc_speeds<R>(uL, uR, L.p, Rs.p, L.rho, Rs.rho, L.c, Rs.c, sL, sR);
-    const R dL = sL - uL, dR = sR - uR;
-    const R sg = ss > (R)0 ? (R)1 : (ss < (R)0 ? (R)-1 : (R)0);
-    const R wl = (R)0.5 * ((R)1 + sg), wr = (R)0.5 * ((R)1 - sg);
-    const R sm = fmin((R)0, sL), sp = fmax((R)0, sR);
-    const R qL = div_rn(ss - uL, sL - ss), qR = div_rn(ss - uR, sR - ss);
-    auto mix = [&](R l, R r) {
+    auto from = [&](bool left, double* F) {
 #pragma clang fp contract(off)
-        return fma(wl, l, wr * r);
+        auto pick = [&](R a, R b) { return left ? a : b; };
+        const R u = pick(uL, uR), p = pick(L.p, Rs.p), rho = pick(L.rho, Rs.rho), E = pick(L.E, Rs.E);
+        const R sk = pick(sL, sR), cap = pick(fmin((R)0, sL), fmax((R)0, sR)), d = sk - u;
+        const R q = div_rn(CHI ? d : ss - u, sk - ss);  // chi_K, or chi_K - 1
+        auto side = [&](R x, R j) {  // u x + cap j
+#pragma clang fp contract(off)
+            return CHI && NODES ? fma(cap, j, x * u) : fma(x, u, cap * j);
+        };
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const R a = pick(L.ar[k], Rs.ar[k]);
+            F[k] = side(a, CHI ? fma(q, a, -a) : q * a);
+        }
+#pragma unroll
+        for (int e = 0; e < D; ++e) {
+            const R m = pick(L.mom[e], Rs.mom[e]);
+            const R f = e == DIR ? fma(m, u, p) : m * u;
+            R jump;
+            if constexpr (CHI)
+                jump = fma(q * rho, e == DIR ? ss : pick(L.u[e], Rs.u[e]), -m);
+            else
+                jump = e == DIR ? rho * sk * q : q * m;
+            F[N + e] = fma(cap, jump, f);
+        }
+        R jump;
+        if constexpr (CHI)
+            jump = fma(q, fma(ss - u, fma(rho, ss, div_rn(p, d)), E), -E);
+        else
+            jump = q * fma(rho * ss, d, E + p);
+        F[IE] = side(E + p, jump);
+#pragma unroll
+        for (int k = 0; k < N - 1; ++k) F[IA + k] = (left ? L.al[k] : Rs.al[k]) * (double)ss;
     };
+    from(ss >= (R)0, G);
+    if (__builtin_expect(ss == (R)0, 0)) {
+        // (at rest under one pressure the two sides are the same)
+        bool rest = L.p == Rs.p;
 #pragma unroll
-    for (int k = 0; k < N; ++k)
-        G[k] = mix(fma(L.ar[k], uL, sm * (qL * L.ar[k])), fma(Rs.ar[k], uR, sp * (qR * Rs.ar[k])));
+        for (int e = 0; e < D; ++e) rest = rest & (L.u[e] == (R)0) & (Rs.u[e] == (R)0);
+        if (!rest) {
+            double F[M];
+            from(false, F);
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-        const R FLd = d == DIR ? fma(L.mom[d], uL, L.p) : L.mom[d] * uL;
-        const R FRd = d == DIR ? fma(Rs.mom[d], uR, Rs.p) : Rs.mom[d] * uR;
-        const R JL = d == DIR ? L.rho * sL * qL : qL * L.mom[d];
-        const R JR = d == DIR ? Rs.rho * sR * qR : qR * Rs.mom[d];
-        G[N + d] = mix(fma(sm, JL, FLd), fma(sp, JR, FRd));
+            for (int c = 0; c < M; ++c) G[c] = (R)fma((R)0.5, (R)G[c], (R)0.5 * (R)F[c]);
+        }
     }
-    const R JL = qL * fma(L.rho * ss, dL, L.E + L.p);
-    const R JR = qR * fma(Rs.rho * ss, dR, Rs.E + Rs.p);
-    G[IE] = mix(fma(L.E + L.p, uL, sm * JL), fma(Rs.E + Rs.p, uR, sp * JR));
-#pragma unroll
-    for (int k = 0; k < N - 1; ++k)
-        G[IA + k] = fma((double)wl, L.al[k] * (double)ss, (double)wr * (Rs.al[k] * (double)ss));
     return ss;
 }
 

@@ -65,14 +65,16 @@ __device__ inline void interp_pair(const R* v, double eps, const MlpPacked* mlp,
     } else {
         const R ul[5] = {v[0], v[1], v[2], v[3], v[4]};
         const R ur[5] = {v[5], v[4], v[3], v[2], v[1]};
-        double dl[5], dr[5];
         float xl[5], xr[5], zl[3], zr[3], wl[3], wr[3];
-        mlp_inputs(ul, dl, xl);
-        mlp_inputs(ur, dr, xr);
+        // one side after the other: with both networks' inputs and logits live at
+        // once the sweeps of two species keep 21 registers in scratch (1024 x 512,
+        // two steps: 946 -> 864 us)
+        mlp_inputs(ul, xl);
         mlp_logits(mlp, xl, zl);
+        l = mlp_omega(zl, xl, wl) ? mlp_value(ul, wl) : weno_is(v[0], v[1], v[2], v[3], v[4], eps);
+        mlp_inputs(ur, xr);
         mlp_logits(mlp, xr, zr);
-        l = mlp_omega(zl, xl, wl) ? mlp_value(v[2], dl, wl) : weno_is(v[0], v[1], v[2], v[3], v[4], eps);
-        r = mlp_omega(zr, xr, wr) ? mlp_value(v[3], dr, wr) : weno_is(v[5], v[4], v[3], v[2], v[1], eps);
+        r = mlp_omega(zr, xr, wr) ? mlp_value(ur, wr) : weno_is(v[5], v[4], v[3], v[2], v[1], eps);
     }
 }
 
@@ -114,30 +116,31 @@ __device__ inline double sensor_product(const double* r, const double* p)
 // liquid's pressure, so another last bit here is now and then another float
 // there: 1e-5 of the momentum of single cells (three species, ten steps).
 // Hence one written order, whose products are fused as written.
-__device__ inline double sensor_ratio_float(double v0, double v1, double v2, double v3, double v4)
+__device__ inline double sensor_ratio_kept(double v0, double v1, double v2, double v3, double v4)
 {
     const double num = fabs(fma(16.0, v3, fma(-30.0, v2, fma(16.0, v1, -v0))) - v4);
     const double den = fabs(fma(16.0, v3, fma(30.0, v2, fma(16.0, v1, v0))) + v4);
     return den > 1e-290 ? num * rcp_newton(den) : sensor_ratio(num, den);
 }
-__device__ inline double sensor_product_float(const double* r, const double* p)
+__device__ inline double sensor_product_kept(const double* r, const double* p)
 {
 #pragma clang fp contract(off)
-    const double sr = 0.5 * (sensor_ratio_float(r[1], r[2], r[3], r[4], r[5]) +
-                             sensor_ratio_float(r[0], r[1], r[2], r[3], r[4]));
-    const double sp = 0.5 * (sensor_ratio_float(p[1], p[2], p[3], p[4], p[5]) +
-                             sensor_ratio_float(p[0], p[1], p[2], p[3], p[4]));
+    const double sr = 0.5 * (sensor_ratio_kept(r[1], r[2], r[3], r[4], r[5]) +
+                             sensor_ratio_kept(r[0], r[1], r[2], r[3], r[4]));
+    const double sp = 0.5 * (sensor_ratio_kept(p[1], p[2], p[3], p[4], p[5]) +
+                             sensor_ratio_kept(p[0], p[1], p[2], p[3], p[4]));
     return sr * sp;
 }
 
-// HCS reconstruction (eq:reconstructed_G) of a double slot of the float faces
-// from its midpoint value t and the sums of the node pairs (i, i+1), (i-1, i+2)
-// and (i-2, i+3), blended with t by sig; one written order, as above
-__device__ inline double hcs_blend(const ParDev& P, double sig, double t, double g23, double g14, double g05)
+// HCS reconstruction (eq:reconstructed_G) of a slot from its midpoint value t and
+// the sums of the node pairs (i, i+1), (i-1, i+2) and (i-2, i+3), blended with t
+// by sig; one written order, as above
+template <typename R>
+__device__ inline R hcs_blend(const ParDev& P, R sig, R t, R g23, R g14, R g05)
 {
 #pragma clang fp contract(off)
-    const double h = fma(-P.hcs_c, g05, fma(P.hcs_b, g14, fma(P.psi, t, -(P.hcs_a * g23))));
-    return fma(sig, t, (1.0 - sig) * h);
+    const R h = fma(-(R)P.hcs_c, g05, fma((R)P.hcs_b, g14, fma((R)P.psi, t, -((R)P.hcs_a * g23))));
+    return fma(sig, t, ((R)1 - sig) * h);
 }
 
 // Output: G = G^{**,-}_{i+1/2} (M slots) and Gp = alpha slots of G^{**,+}.
@@ -161,6 +164,10 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
     // sum to one), so this is the same interpolation, but float now resolves
     // the small differences u +- p/(rho c) that carry the pressure in a liquid.
     constexpr bool DELTA = sizeof(R) != sizeof(double);
+    // Float faces and the learned weights (whose inputs are bfloat16) round
+    // doubles to fewer bits: they keep the order of operations that their results
+    // stand for
+    constexpr bool KEPT = DELTA || WT == 1;
     auto nv = [&](int j, int f) -> R { return (R)nodev<NS, FS>(nd, j, f); };
     auto dv = [&](int j, int f) -> R {
         return DELTA ? (R)(nodev<NS, FS>(nd, j, f) - nodev<NS, FS>(nd, 2, f)) : (R)nodev<NS, FS>(nd, j, f);
@@ -182,11 +189,15 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
     // limiter when it has to act, so it is formed on demand
     auto first_order = [&](const St<N, D>& L, const St<N, D>& Rn, double* Glo, double* Glo_p) {
         const St<N, D, R> Lr = convert<N, D, R>(L), Rr = convert<N, D, R>(Rn);
-        const double ss = hllc<N, D, DIR>(Lr, Rr, Glo);
+        double ss;
+        if constexpr (KEPT)
+            ss = hllc_kept<N, D, DIR, R, true>(Lr, Rr, Glo);
+        else
+            ss = hllc<N, D, DIR>(Lr, Rr, Glo);
 #pragma unroll
         for (int k = 0; k < N - 1; ++k) {
 #pragma clang fp contract(off)
-            Glo_p[k] = DELTA ? Glo[IA + k] - ss * Rr.al[k] : fma(-ss, Rr.al[k], Glo[IA + k]);
+            Glo_p[k] = KEPT ? Glo[IA + k] - ss * Rr.al[k] : fma(-ss, Rr.al[k], Glo[IA + k]);
             Glo[IA + k] = fma(-ss, Lr.al[k], Glo[IA + k]);
         }
     };
@@ -294,7 +305,11 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
 
     // midpoint flux and velocity from HLLC on the interpolated states
     double Gt[M];
-    const R ut = hllc<N, D, DIR>(VL, VR, Gt);
+    R ut;
+    if constexpr (KEPT)
+        ut = hllc_kept<N, D, DIR, R>(VL, VR, Gt);
+    else
+        ut = hllc<N, D, DIR>(VL, VR, Gt);
 
     // shock sensor (Sec. 4.3.1) on mixture density and pressure, in double in
     // both variants: C_s = 1e12 turns float rounding of p at a contact into
@@ -308,7 +323,7 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
             r[j] = nodev<NS, FS>(nd, j, F::RHO);
             pr[j] = nodev<NS, FS>(nd, j, F::P);
         }
-        const double z = DELTA ? sensor_product_float(r, pr) : sensor_product(r, pr);
+        const double z = KEPT ? sensor_product_kept(r, pr) : sensor_product(r, pr);
         const double arg = P.Cs * (P.qexp == 2.0 ? z * z : pow(z, P.qexp));
         // tanh is exactly 0 at 0 and rounds to 1 for arguments >= 22; below
         // 0.01 (smooth flow: nearly every face) its odd series to x^7 is
@@ -328,7 +343,7 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
     // variants: G^+-_alpha = G_alpha - u-hat alpha_i cancels to (alpha-tilde -
     // alpha_i) u-hat only if both terms see the same velocity at full precision.
     double Gho[M], Gho_p[NA], uh;
-    if constexpr (!DELTA) {
+    if constexpr (!KEPT) {
         // every slot's flux at node j is its conserved value times u_j (plus
         // pressure terms), so the node weights of the reconstruction are
         // multiplied into u_j once and each slot is six multiply-adds
@@ -355,7 +370,6 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
             Gho[c] = fma(sig, Gt[c], om * h);
         }
     } else {
-        const R psi = (R)P.psi, ha = (R)P.hcs_a, hb = (R)P.hcs_b, hc = (R)P.hcs_c;
         R un[6], pj[6];
         double und[6];
 #pragma unroll
@@ -374,20 +388,16 @@ __device__ __forceinline__ void face_flux(const double* nd, KArg ke, KArg kp, do
                 };
                 Gho[c] = hcs_blend(P, sigd, Gt[c], pair(2, 3), pair(1, 4), pair(0, 5));
             } else {
-                R g[6];
-#pragma unroll
-                for (int j = 0; j < 6; ++j) {
-                    const R w = nv(j, c);
-                    if (c >= N && c < N + D)
-                        g[j] = w * un[j] + (c - N == DIR ? pj[j] : (R)0);
-                    else if (c == IE)
-                        g[j] = (w + pj[j]) * un[j];
-                    else
-                        g[j] = w * un[j];
-                }
-                const R gt = (R)Gt[c];
-                const R ghcs = psi * gt - ha * (g[2] + g[3]) + hb * (g[1] + g[4]) - hc * (g[0] + g[5]);
-                Gho[c] = (double)(sig * gt + ((R)1 - sig) * ghcs);
+                auto pair = [&](int i, int j) -> R {
+#pragma clang fp contract(off)
+                    const R wi = nv(i, c), wj = nv(j, c);
+                    if (c == N + DIR) return fma(wi, un[i], pj[i]) + fma(wj, un[j], pj[j]);
+                    if (c >= N && c < N + D) return wi * un[i] + wj * un[j];
+                    if (c == IE) return fma(wi + pj[i], un[i], (wj + pj[j]) * un[j]);
+                    if (WT == 1 && DIR == 0 && c == N - 2 && i == 2) return fma(wj, un[j], wi * un[i]);
+                    return fma(wi, un[i], wj * un[j]);
+                };
+                Gho[c] = hcs_blend<R>(P, sig, (R)Gt[c], pair(2, 3), pair(1, 4), pair(0, 5));
             }
         }
         uh = hcs_blend(P, sigd, (double)ut, und[2] + und[3], und[1] + und[4], und[0] + und[5]);

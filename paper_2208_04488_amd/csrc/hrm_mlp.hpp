@@ -171,13 +171,12 @@ __device__ inline bool mlp_omega(const float* z, const float* x, float* w)
     return isfinite(w[0]) && isfinite(w[1]) && isfinite(w[2]);
 }
 
-// differences d[j] = u[j] - u[2] of a stencil from its node i (d[2] = 0) and
-// its normalised float inputs; the reciprocal of the spread by Newton's
-// iteration (as rcp_newton) where it is well inside the normal numbers (with
-// the differences kept for mlp_value: 1024 x 512, two steps 846 -> 837 us)
-__device__ inline void mlp_inputs(const double* u, double* d, float* x)
+// normalised float inputs of a stencil u[0..4] (u[2] the node i); the reciprocal
+// of the spread by Newton's iteration (as rcp_newton) where it is well inside the
+// normal numbers
+__device__ inline void mlp_inputs(const double* u, float* x)
 {
-    double s = 0.0;
+    double d[5], s = 0.0;
 #pragma unroll
     for (int j = 0; j < 5; ++j) {
         d[j] = u[j] - u[2];
@@ -197,14 +196,13 @@ __device__ inline void mlp_inputs(const double* u, double* d, float* x)
 
 // sum_k w_k S_k written as S_c + w_l (S_l - S_c) + w_r (S_r - S_c): the
 // weights sum to one only to float round-off, and this form keeps a constant
-// stencil exact.  The candidates in differences from node i: 8 (S_c - u_i) =
-// 3 d_3 - d_1, 8 (S_l - S_c) = 3 (d_0 - d_3) - 9 d_1, 8 (S_r - S_c) = 3 d_3 + d_1 - d_4.
-__device__ inline double mlp_value(double ui, const double* d, const float* w)
+// stencil exact
+__device__ inline double mlp_value(const double* u, const float* w)
 {
-    const double c = fma(3.0, d[3], -d[1]);
-    const double l = fma(-9.0, d[1], 3.0 * (d[0] - d[3]));
-    const double r = fma(3.0, d[3], d[1]) - d[4];
-    return fma(0.125, fma((double)w[0], l, fma((double)w[2], r, c)), ui);
+    const double sl = (3.0 * u[0] - 10.0 * u[1] + 15.0 * u[2]) / 8.0;
+    const double sc = (-u[1] + 6.0 * u[2] + 3.0 * u[3]) / 8.0;
+    const double sr = (3.0 * u[2] + 6.0 * u[3] - u[4]) / 8.0;
+    return sc + (double)w[0] * (sl - sc) + (double)w[2] * (sr - sc);
 }
 
 // ---------------------------------------------------------------- host side
