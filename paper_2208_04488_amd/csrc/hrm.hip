@@ -681,8 +681,8 @@ __global__ void __launch_bounds__(256) k_relax(double* W, long long nc, EosDev e
 // Sec. 3: p*, T* (eq:p_relax, eq:T_relax_e) and the sound speed of the
 // four-equation HRM (eq:4_eqn_sos) of every cell; NaN where the state has
 // no admissible relaxed state.  Null outputs are skipped.  p* and T* are
-// evaluated once for all outputs; the kernel is bound by its arithmetic
-// (2048 x 1280, two species: 36 -> 27.7 us).
+// evaluated once for all outputs (2048 x 1280, two species: 36 -> 27.7 us);
+// the kernel is now bound by memory: 168 MB in that time, 6.1 TB/s.
 template <int N, int D, int V>
 __global__ void __launch_bounds__(256) k_equilibrium(const double* W, long long nc, EosDev e, double* p_out,
                                                       double* T_out, double* c_out)
@@ -1200,6 +1200,11 @@ int check_boundary(hrm_ctx* c);
 // 215 000 cells), where it beats the two sweeps (us a step, sweeps / k_plane, two
 // species: 127 x 65 62 / 36, 300 x 200 78 / 62, 500 x 300 114 / 94, 700 x 350 144 / 131,
 // 1024 x 512 211 / 231; three species: 76 / 43, 93 / 74, 135 / 119, 175 / 169, 255 / 294).
+// The limit is eight tiles a CU, between 500 x 300 (1462 tiles: it leads by 13 to
+// 21 %) and 700 x 350 (2350 tiles: still 4 to 10 %).  The curves cross above it,
+// before 1024 x 512, between sizes that were not timed.  With float faces and three
+// species, planes of 16 cells across and over 6000 along are 3 % slower here than
+// by the sweeps.
 // The first-order schemes, the learned weights and runs with the launch timers on,
 // which want the sweeps one by one, are left to the sweeps.
 bool plane_fits(const hrm_ctx* c)

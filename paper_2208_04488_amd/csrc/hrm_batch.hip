@@ -83,7 +83,10 @@ __global__ void __launch_bounds__(BS, 3) k_batch(const BatchArgs A)
     const long long T = A.T;
     const bool narrow = BS == 512 && (int)blockIdx.x < A.narrow;
     const int bs = narrow ? 256 : BS;
-    if (ts >= bs) return;  // whole waves; the barriers count those that are left
+    // whole waves end here, before the barriers below.  That rests on the hardware, whose
+    // barrier counts the workgroup's living waves; the language promises it only for
+    // barriers that every thread reaches
+    if (ts >= bs) return;
 
     for (;;) {
         if (ts == 0) {

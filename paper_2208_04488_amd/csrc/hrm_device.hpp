@@ -565,9 +565,9 @@ __device__ inline void set_rc2(KArg ke, St<N, D>& s)
 // below would leave it as it is, without looking at the node: every partial
 // density and volume fraction at or above eps (then b >= eps >= min(eps, a):
 // no blending, and with eps >= eps^HS no hard switch), rho c^2 positive and at
-// or above eps^HS, and everything finite (an infinite or NaN slot leaves a bound unmet
-// or makes E or rho c^2 infinite or NaN).  Most faces pass; the nodes are
-// read from LDS and the limiter runs only where one does not.
+// or above eps^HS, and everything finite (an infinite or NaN slot leaves a
+// bound unmet or makes E or rho c^2 infinite or NaN).  Most faces pass; the
+// nodes are read from LDS and the limiter runs only where one does not.
 template <int N, int D, int DIR, typename R>
 __device__ inline bool interp_clean(KArg ke, KArg kp, St<N, D, R>& V)
 {

@@ -111,11 +111,11 @@ __device__ inline double sensor_product(const double* r, const double* p)
            (sensor_ratio(n[2], d[2]) + sensor_ratio(n[3], d[3]));
 }
 
-// The same product for float faces, ratio by ratio.  The blending weight that
-// comes of it is rounded to float and multiplies fluxes of the size of a
-// liquid's pressure, so another last bit here is now and then another float
-// there: 1e-5 of the momentum of single cells (three species, ten steps).
-// Hence one written order, whose products are fused as written.
+// The same product ratio by ratio, for float faces and learned weights.  The
+// blending weight that comes of it is rounded to float and multiplies fluxes of
+// the size of a liquid's pressure, so another last bit here is now and then
+// another float there: 1e-5 of the momentum of single cells (three species, ten
+// steps).  Hence one written order, whose products are fused as written.
 __device__ inline double sensor_ratio_kept(double v0, double v1, double v2, double v3, double v4)
 {
     const double num = fabs(fma(16.0, v3, fma(-30.0, v2, fma(16.0, v1, -v0))) - v4);
